@@ -24,8 +24,8 @@
  * for the handle's lifetime.  The buffer is device memory or pinned host
  * memory (hipHostMalloc, or torch's pin_memory); create() asks the HIP
  * runtime which one and rejects anything else.  Pack and unpack copy bytes
- * only; tensors whose address and the buffer are 16-byte aligned take the
- * vector path, others a byte path.  Bytes of the buffer between pieces are
+ * only, 16 at a time wherever a tensor or piece starts (its first and last
+ * few bytes singly).  Bytes of the buffer between pieces are
  * never written.  Pack and unpack are asynchronous on the caller's stream:
  * host code that touches a pinned host buffer waits for the stream first.
  * Status codes are rl_da_status (rl_decode_attn.h).

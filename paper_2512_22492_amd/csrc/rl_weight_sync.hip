@@ -5,7 +5,8 @@
 // Plan on the host, copy on the GPU.  A chunk's pieces are cut into 32 KiB
 // tiles; one work-group of 256 threads copies one tile, each thread eight
 // 16-byte vectors with all loads issued before the stores (non-temporal
-// loads, and non-temporal stores into device memory).  A work-group finds
+// loads from any byte address, and non-temporal aligned stores into device
+// memory).  A work-group finds
 // its piece by binary search over the pieces' first-tile numbers, so pieces of
 // any size share one launch.  The copy is bound by HBM (read + write of every
 // byte) when the buffer is device memory and by the host link when it is
@@ -40,6 +41,24 @@ struct CopyArgs {
     int32_t unpack;           // 0: tensor -> buffer, 1: buffer -> tensor
 };
 
+// Any piece moves as 16-byte vectors, whatever its source and destination
+// addresses: a piece of a flat shard starts at any element, so its address
+// modulo 16 matches the buffer's only by luck.  Tiles are cut where the
+// destination is aligned, the stores are aligned, and the loads start at any
+// byte: the copy is bound by HBM either way (four Qwen3-8B layers' sixth, 257 MB
+// in pieces 14 bytes off, packed and unpacked: 169 us, 6.07 TB/s read + write;
+// copied byte by byte 551 us, 1.87 TB/s.  Aligned pieces keep 6.17 TB/s).
+
+// A 16-byte load from any byte address (global loads take any alignment on
+// gfx950; the same instruction as an aligned one), non-temporal.
+typedef u32x4_t __attribute__((aligned(1))) u32x4_any_t;
+__device__ __forceinline__ uint4 load_stream16_any(const uint8_t* p)
+{
+    const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any_t*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// Loads may start at any byte, stores are aligned.
 // STREAM_STORES: the destination is device memory and gets non-temporal
 // stores (data written once, not read back soon; into pinned host memory
 // they measured slower).  A template parameter, not a run-time flag: the
@@ -62,14 +81,16 @@ __global__ __launch_bounds__(kCopyThreads) void copy_pieces(CopyArgs a)
     const CopyPiece pc = a.pieces[lo];
     const uint8_t* src = a.unpack ? pc.buffer : pc.tensor;
     uint8_t* dst = a.unpack ? pc.tensor : pc.buffer;
-    const uint64_t begin = (tile - pc.first_tile) * kTileBytes;
+    // Tiles start where the destination is 16-byte aligned: the head of fewer
+    // than 16 bytes before that belongs to the first tile, the rest of fewer
+    // than 16 bytes to the last.
+    const uint64_t head = (uint64_t)(-(intptr_t)dst & 15);
+    const uint64_t first = (tile - pc.first_tile) * kTileBytes;
+    const uint64_t begin = head + first < pc.nbytes ? head + first : pc.nbytes;
     const uint64_t end = pc.nbytes < begin + kTileBytes ? pc.nbytes : begin + kTileBytes;
     const int t = threadIdx.x;
-    if ((((uintptr_t)src | (uintptr_t)dst) & 15) != 0) {
-        for (uint64_t i = begin + t; i < end; i += kCopyThreads)
-            dst[i] = src[i];
-        return;
-    }
+    if (first == 0 && t < (int)begin)  // begin = min(head, nbytes)
+        dst[t] = src[t];
     const uint64_t nvec = (end - begin) / 16;
     const uint8_t* s = src + begin;
     uint4* d = reinterpret_cast<uint4*>(dst + begin);
@@ -77,7 +98,7 @@ __global__ __launch_bounds__(kCopyThreads) void copy_pieces(CopyArgs a)
         uint4 v[kVecPerThread];
 #pragma unroll
         for (int i = 0; i < kVecPerThread; ++i)
-            v[i] = load_stream16(s + 16 * (t + i * kCopyThreads));
+            v[i] = load_stream16_any(s + 16 * (t + i * kCopyThreads));
 #pragma unroll
         for (int i = 0; i < kVecPerThread; ++i) {
             if (STREAM_STORES) {
@@ -90,7 +111,7 @@ __global__ __launch_bounds__(kCopyThreads) void copy_pieces(CopyArgs a)
         return;
     }
     for (uint64_t i = t; i < nvec; i += kCopyThreads)
-        d[i] = load_stream16(s + 16 * i);
+        d[i] = load_stream16_any(s + 16 * i);
     for (uint64_t i = begin + 16 * nvec + t; i < end; i += kCopyThreads)
         dst[i] = src[i];
 }

@@ -87,6 +87,43 @@ def test_pack_unpack_misaligned_tensors(case):
     run_plan(sizes, cap, align, seed=10 + case, misalign={1, 2})
 
 
+TILE = 32768  # bytes a work-group copies
+
+
+@pytest.mark.parametrize("pinned", [False, True])
+@pytest.mark.parametrize("offset", [1, 2, 8, 14, 15])
+def test_pack_unpack_pieces_at_any_address(offset, pinned):
+    """Tensors `offset` bytes into their allocation, packed at align 1 (so the
+    buffer addresses take every residue too), of sizes around a vector and a
+    copy tile, with the bytes around each tensor left alone."""
+    sizes = [1, 15, 16, 17, 31, TILE - 1, TILE, TILE + 1, TILE + 15, TILE + 17, 2 * TILE + 30,
+             3 * TILE, 5]
+    rng = np.random.default_rng(offset)
+    host = [rng.integers(0, 256, n, dtype=np.uint8) for n in sizes]
+    base = [torch.full((n + 32,), SENTINEL, dtype=torch.uint8, device=device()) for n in sizes]
+    back = [t.clone() for t in base]
+    for t, h in zip(base, host):
+        t[offset:offset + h.size] = torch.from_numpy(h).to(device())
+    cap = 3 * TILE + 100
+    buf = (torch.empty(cap, dtype=torch.uint8, pin_memory=True) if pinned
+           else torch.empty(cap, dtype=torch.uint8, device=device()))
+    pieces = WS.plan(sizes, cap, 1)
+    views = [[t[offset:offset + n] for t, n in zip(ts, sizes)] for ts in (base, back)]
+    with B.WeightSync(views[0], buf, align=1) as ws, B.WeightSync(views[1], buf, align=1) as rx:
+        for c in range(ws.num_chunks):
+            buf.fill_(SENTINEL)
+            ws.pack(c)
+            torch.cuda.synchronize()
+            want, _ = WS.pack(host, pieces, c, cap, fill=SENTINEL)
+            assert np.array_equal(host_bytes(buf), want), "chunk %d" % c
+            rx.unpack(c)
+            torch.cuda.synchronize()
+    for t, h in zip(back, host):
+        got = host_bytes(t)
+        assert np.array_equal(got[offset:offset + h.size], h)
+        assert np.all(got[:offset] == SENTINEL) and np.all(got[offset + h.size:] == SENTINEL)
+
+
 @pytest.mark.parametrize("case", [0, 2])
 def test_pack_unpack_pinned_host_buffer(case):
     """The checkpoint form: the buffer lives in pinned host memory."""
