@@ -68,6 +68,27 @@ enum Schedule : int32_t {
     kQueuePlanned = 2,  // persistent, units longest first from the LDS plan
 };
 
+// How many pages each split of a sequence takes: `pages` for one that fills the
+// handle's table, and down to min_pages for a shorter one, so that it spreads
+// over the partials its rows have anyway (slots of them).  Sequences of up to
+// `whole` pages are not cut more finely than `pages`.  A function of the
+// sequence's own length and of the handle, never of the batch.
+struct SplitRule {
+    int32_t pages;      // the handle's split size
+    int32_t min_pages;  // == pages: every split takes that many
+    int32_t whole;      // 0 or pages
+    int32_t slots;      // splits of a sequence that fills the handle's table
+    __host__ __device__ bool by_length() const { return min_pages != pages; }
+    __host__ __device__ int pages_of(int npages) const
+    {
+        if (!by_length() || npages <= whole)
+            return pages;
+        const int even = (npages + slots - 1) / slots;
+        const int p = even > min_pages ? even : min_pages;
+        return p < pages ? p : pages;
+    }
+};
+
 struct SplitArgs {
     const uint16_t* q;          // bf16 bits [B][Hq][D]
     const uint8_t* k_pool;      // [P][Hkv][16][D] or [P][16][Hkv][D] elements
@@ -87,8 +108,8 @@ struct SplitArgs {
     int32_t num_q_heads;
     int32_t num_kv_heads;
     int32_t max_pages;
-    int32_t split_pages;
-    int32_t num_splits;         // ceil(max_pages / split_pages)
+    SplitRule rule;
+    int32_t num_splits;         // most splits of a sequence of max_pages pages
     int32_t heads_per_unit;     // kv heads per head-parallel work-group
     int32_t batch;
     int32_t schedule;           // several splits: a Schedule
@@ -102,6 +123,7 @@ struct WaveTask {
     int seq_len;   // clamped to max_pages * page_size
     int npages;    // pages holding the sequence
     int nsplit;    // splits of this sequence
+    int split_pages;  // pages of each but the last
     int p0;        // first page of the unit
     int count;     // pages of this wavefront (may be 0)
     bool owner;    // the one unit per (sequence, head) that writes an empty
@@ -124,13 +146,15 @@ __device__ __forceinline__ bool begin_unit(const SplitArgs& a, WaveTask& t, int3
     t.kvh = kvh;
     t.owner = owner;
     t.s = max(s, 0);
-    t.p0 = t.s * a.split_pages;
+    t.split_pages = a.rule.pages;
+    t.p0 = t.s * t.split_pages;
     auto load_pages = [&] {
         const int col = t.p0 + t.wave + kUnitWaves * t.lane;
-        const bool in_split = col < t.p0 + a.split_pages && col < a.max_pages;
+        const bool in_split = col < t.p0 + t.split_pages && col < a.max_pages;
         my_page = in_split ? a.block_table[(int64_t)t.b * a.max_pages + col] : 0;
     };
-    if (s >= 0)
+    const bool early = s >= 0 && !a.rule.by_length();
+    if (early)
         load_pages();  // issued together with the length load
     int L = a.seq_lens[t.b];
     const int cap = a.max_pages * kPageSize;
@@ -141,17 +165,17 @@ __device__ __forceinline__ bool begin_unit(const SplitArgs& a, WaveTask& t, int3
     }
     t.seq_len = L;
     t.npages = L > 0 ? (L + kPageSize - 1) / kPageSize : 0;
-    t.nsplit = (t.npages + a.split_pages - 1) / a.split_pages;
-    if (s < 0) {
-        if (t.nsplit == 0)
-            return false;
+    t.split_pages = a.rule.pages_of(t.npages);
+    t.nsplit = (t.npages + t.split_pages - 1) / t.split_pages;
+    if (s < 0)
         t.s = t.nsplit - 1;
-        t.p0 = t.s * a.split_pages;
-        load_pages();
-    } else if (t.s >= t.nsplit) {
+    if (t.s < 0 || t.s >= t.nsplit)
         return false;
+    if (!early) {
+        t.p0 = t.s * t.split_pages;
+        load_pages();
     }
-    const int p1 = min(t.p0 + a.split_pages, t.npages);
+    const int p1 = min(t.p0 + t.split_pages, t.npages);
     t.count = max(0, (p1 - t.p0 - t.wave + kUnitWaves - 1) / kUnitWaves);
     if (CHECKED) {
         const bool bad = t.lane < t.count && (my_page < 0 || (int64_t)my_page >= a.num_pages);
@@ -243,10 +267,11 @@ __device__ __forceinline__ void split_shape(const SplitArgs& a, int b, int& full
 {
     const int L = min(a.seq_lens[b], a.max_pages * kPageSize);
     const int np = L > 0 ? (L + kPageSize - 1) / kPageSize : 0;
-    const int ns = (np + a.split_pages - 1) / a.split_pages;
+    const int sp = a.rule.pages_of(np);
+    const int ns = (np + sp - 1) / sp;
     full = max(ns - 1, 0);
-    const int last = ns > 0 ? np - (ns - 1) * a.split_pages : 0;  // 0 .. split_pages
-    cls = (a.split_pages - last) * kLengthClasses / (a.split_pages + 1);
+    const int last = ns > 0 ? np - (ns - 1) * sp : 0;  // 0 .. sp <= rule.pages
+    cls = (a.rule.pages - last) * kLengthClasses / (a.rule.pages + 1);
 }
 
 // Exclusive prefix over the work-group's threads of K counts per thread, in
@@ -961,12 +986,12 @@ __device__ __forceinline__ bool begin_unit_hp(const SplitArgs& a, WaveTask& t, i
     t.b = b;
     t.owner = owner;
     t.s = max(s, 0);
-    t.p0 = t.s * a.split_pages;
+    t.p0 = t.s * a.rule.pages;
     // the first kWave pages' block-table entries (later ones are loaded as
     // the wavefront reaches them)
     auto load_pages = [&] {
         const int col = t.p0 + t.lane;
-        const bool in_split = t.lane < a.split_pages && col < a.max_pages;
+        const bool in_split = t.lane < a.rule.pages && col < a.max_pages;
         my_page = in_split ? a.block_table[(int64_t)t.b * a.max_pages + col] : 0;
     };
     if (s >= 0)
@@ -980,15 +1005,15 @@ __device__ __forceinline__ bool begin_unit_hp(const SplitArgs& a, WaveTask& t, i
     }
     t.seq_len = L;
     t.npages = L > 0 ? (L + kPageSize - 1) / kPageSize : 0;
-    t.nsplit = (t.npages + a.split_pages - 1) / a.split_pages;
+    t.nsplit = (t.npages + a.rule.pages - 1) / a.rule.pages;
     if (s < 0) {
         if (t.nsplit == 0)
             return false;
         t.s = t.nsplit - 1;
-        t.p0 = t.s * a.split_pages;
+        t.p0 = t.s * a.rule.pages;
         load_pages();
     }
-    const int p1 = min(t.p0 + a.split_pages, t.npages);
+    const int p1 = min(t.p0 + a.rule.pages, t.npages);
     if (t.p0 >= p1)
         return false;
     t.count = p1 - t.p0;
@@ -1514,12 +1539,21 @@ __attribute__((amdgpu_waves_per_eu(G > 4 || PERSISTENT ? 2 : 3))) void split_pv(
 
 // -------------------------------------------------------- merge kernel ---
 //
-// One work-group of four wavefronts per (b, h) of sequences with more than one
-// split: M = max_s m_s, then wavefront w sums w_s l_s and w_s acc_s
-// (w_s = 2^(m_s - M)) over splits s = w, w+4, ... (two dims per lane), and the
-// four partial sums are added in wavefront order.
+// One work-group of four wavefronts per `rows` query heads (b, h..) of
+// sequences with more than one split.  Each row: M = max_s m_s, then
+// wavefront w sums w_s l_s and w_s acc_s (w_s = 2^(m_s - M)) over splits s = w,
+// w+4, ... (two dims per lane), and the four partial sums are added in
+// wavefront order.
+//
+// A launch whose handle allows several splits may hold only sequences of one:
+// its work-groups find that from the length alone and leave, so what such a
+// launch costs is its number of work-groups (200 sequences x 64 heads, all of
+// one split: 7.8 us with a
+// work-group a row; the step 58.4 -> 54.2 us).  Hence several rows of a sequence per work-group once
+// there are more rows than keep the chip busy (kMergeGroups).
 
 constexpr int kMergeWaves = 4;
+constexpr int64_t kMergeGroups = 1024;
 
 struct MergeArgs {
     const int32_t* seq_lens;
@@ -1528,72 +1562,97 @@ struct MergeArgs {
     uint16_t* out;
     int32_t num_q_heads;
     int32_t max_pages;
-    int32_t split_pages;
+    SplitRule rule;
     int32_t num_splits;
+    int32_t rows;  // per work-group; divides num_q_heads
 };
+
+// Rows per work-group: doubled while they divide the heads and leave at least
+// kMergeGroups work-groups.
+int merge_rows(int64_t batch, int num_q_heads)
+{
+    int rows = 1;
+    while (num_q_heads % (2 * rows) == 0 && batch * num_q_heads / (2 * rows) >= kMergeGroups)
+        rows *= 2;
+    return rows;
+}
 
 __global__ __launch_bounds__(kWave * kMergeWaves) void merge_splits(MergeArgs a)
 {
     __shared__ float part[kMergeWaves][kHeadDim + 1];
-    const int64_t row = blockIdx.x;  // b * Hq + h
-    const int b = (int)(row / a.num_q_heads);
+    const int64_t row0 = (int64_t)blockIdx.x * a.rows;  // b * Hq + h
+    const int b = (int)(row0 / a.num_q_heads);
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const float* ml = a.ws_ml + row * a.num_splits * 2;
-    const float* acc = a.ws_acc + row * a.num_splits * kHeadDim + 2 * lane;
-    // The length and the first loads of both passes go out together (every
-    // split index below num_splits lies inside the row's partials), so the
-    // common case takes one round trip to memory; entries past the
-    // sequence's own splits are read but not used.
+    // A row's first loads of both passes go out together, and in a launch of one
+    // row a work-group (where the round trips count, not the bytes) together with
+    // the length: every split index below num_splits lies inside the row's
+    // partials, and what lies past the sequence's own splits is not used.
+    float m_first;
+    float2 ml_first, v_first;
+    auto first_loads = [&](int64_t row, int splits) {
+        const float* ml = a.ws_ml + row * a.num_splits * 2;
+        const float* acc = a.ws_acc + row * a.num_splits * kHeadDim + 2 * lane;
+        m_first = lane < splits ? ml[2 * lane] : -INFINITY;
+        ml_first = v_first = make_float2(0.0f, 0.0f);
+        if (wave < splits) {
+            ml_first = *reinterpret_cast<const float2*>(ml + 2 * wave);
+            v_first = *reinterpret_cast<const float2*>(acc + (int64_t)wave * kHeadDim);
+        }
+    };
     const int len = a.seq_lens[b];
-    const float m_first = lane < a.num_splits ? ml[2 * lane] : -INFINITY;
-    float2 ml_first = make_float2(0.0f, 0.0f), v_first = make_float2(0.0f, 0.0f);
-    if (wave < a.num_splits) {
-        ml_first = *reinterpret_cast<const float2*>(ml + 2 * wave);
-        v_first = *reinterpret_cast<const float2*>(acc + (int64_t)wave * kHeadDim);
-    }
+    if (a.rows == 1)
+        first_loads(row0, a.num_splits);
     const int L = min(len, a.max_pages * kPageSize);
     const int npages = L > 0 ? (L + kPageSize - 1) / kPageSize : 0;
-    const int n = (npages + a.split_pages - 1) / a.split_pages;
+    const int sp = a.rule.pages_of(npages);
+    const int n = (npages + sp - 1) / sp;
     if (n < 2)
         return;  // finished by the split kernel
-    float M = lane < n ? m_first : -INFINITY;
-    for (int s = lane + kWave; s < n; s += kWave)
-        M = fmaxf(M, ml[2 * s]);
+    for (int64_t row = row0; row < row0 + a.rows; ++row) {
+        const float* ml = a.ws_ml + row * a.num_splits * 2;
+        const float* acc = a.ws_acc + row * a.num_splits * kHeadDim + 2 * lane;
+        if (a.rows > 1)
+            first_loads(row, n);
+        float M = lane < n ? m_first : -INFINITY;
+        for (int s = lane + kWave; s < n; s += kWave)
+            M = fmaxf(M, ml[2 * s]);
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        M = fmaxf(M, __shfl_xor(M, off));
-    // wavefront w: splits w, w+4, ... in order
-    float den = 0.0f, num0 = 0.0f, num1 = 0.0f;
-    if (wave < n) {
-        const float w = exp2_fast(ml_first.x - M);
-        den = fmaf(w, ml_first.y, den);
-        num0 = fmaf(w, v_first.x, num0);
-        num1 = fmaf(w, v_first.y, num1);
-    }
-    for (int s = wave + kMergeWaves; s < n; s += kMergeWaves) {
-        const float w = exp2_fast(ml[2 * s] - M);
-        den = fmaf(w, ml[2 * s + 1], den);
-        const float2 v = *reinterpret_cast<const float2*>(acc + (int64_t)s * kHeadDim);
-        num0 = fmaf(w, v.x, num0);
-        num1 = fmaf(w, v.y, num1);
-    }
-    part[wave][2 * lane] = num0;
-    part[wave][2 * lane + 1] = num1;
-    if (lane == 0)
-        part[wave][kHeadDim] = den;
-    __syncthreads();
-    if (wave != 0)
-        return;
-    float d = 0.0f, x0 = 0.0f, x1 = 0.0f;
+        for (int off = 32; off >= 1; off >>= 1)
+            M = fmaxf(M, __shfl_xor(M, off));
+        // wavefront w: splits w, w+4, ... in order
+        float den = 0.0f, num0 = 0.0f, num1 = 0.0f;
+        if (wave < n) {
+            const float w = exp2_fast(ml_first.x - M);
+            den = fmaf(w, ml_first.y, den);
+            num0 = fmaf(w, v_first.x, num0);
+            num1 = fmaf(w, v_first.y, num1);
+        }
+        for (int s = wave + kMergeWaves; s < n; s += kMergeWaves) {
+            const float w = exp2_fast(ml[2 * s] - M);
+            den = fmaf(w, ml[2 * s + 1], den);
+            const float2 v = *reinterpret_cast<const float2*>(acc + (int64_t)s * kHeadDim);
+            num0 = fmaf(w, v.x, num0);
+            num1 = fmaf(w, v.y, num1);
+        }
+        part[wave][2 * lane] = num0;
+        part[wave][2 * lane + 1] = num1;
+        if (lane == 0)
+            part[wave][kHeadDim] = den;
+        __syncthreads();
+        if (wave == 0) {
+            float d = 0.0f, x0 = 0.0f, x1 = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kMergeWaves; ++w) {
-        d += part[w][kHeadDim];
-        x0 += part[w][2 * lane];
-        x1 += part[w][2 * lane + 1];
+            for (int w = 0; w < kMergeWaves; ++w) {
+                d += part[w][kHeadDim];
+                x0 += part[w][2 * lane];
+                x1 += part[w][2 * lane + 1];
+            }
+            const float inv = 1.0f / d;
+            *reinterpret_cast<uint32_t*>(a.out + row * kHeadDim + 2 * lane) =
+                f32_to_bf16(x0 * inv) | (f32_to_bf16(x1 * inv) << 16);
+        }
+        __syncthreads();  // part is the next row's
     }
-    const float inv = 1.0f / d;
-    *reinterpret_cast<uint32_t*>(a.out + row * kHeadDim + 2 * lane) =
-        f32_to_bf16(x0 * inv) | (f32_to_bf16(x1 * inv) << 16);
 }
 
 // ------------------------------------------------------------ dispatch ---
@@ -1680,6 +1739,40 @@ int default_split_tokens(const rl_da_config* cfg, int64_t units_per_split)
     return st;
 }
 
+// Tokens of the shortest split that a handle with the default split size cuts a
+// sequence into (SplitRule), and whether sequences of up to one default split
+// stay whole.
+//
+// A handle made for a long context has few long sequences in many of its
+// steps.  With 4096-token splits alone, three sequences of 8k..32k tokens x 8
+// heads are 120 units for 256 CUs, each a serial walk of about 110 us that
+// draws 26 KB/us, what one CU keeps in flight: 128.7 us a step, 78.7 us cut by
+// length (357 MB).  The line, from sweeps of the split size on one box:
+//   * up to 128 pairs of (sequence, kv head) even a full batch leaves CUs
+//     idle unless it is cut: 512 (64 x 1 pairs, lengths around 4096: 73.6 us at
+//     4096, 52.3 at 2048, 47.7 at 1024, 44.0 at 512, 44.9 at 256); up to 256
+//     pairs 1024;
+//   * above that a full batch fills the chip and every cut costs it (64 x 8 pairs
+//     of 4096 tokens: 180.3 us whole, 184.1 at 2048, 196.3 at 512), so only
+//     sequences longer than one default split are cut, to 2048 at least;
+//   * and only where the table holds 16 default splits: in one made for its
+//     batch's longest sequence those above half its width take longer splits
+//     than the others and end the launch (128 x 4 pairs, lognormal to 32768
+//     in a table of 32768: 286 us whole, 311 us cut).
+int min_split_tokens(const rl_da_config* cfg, int st, int max_splits, bool head_parallel,
+                     bool* whole)
+{
+    *whole = true;
+    if (cfg->split_tokens != 0 || max_splits == 1 || head_parallel)
+        return st;
+    const int64_t pairs = (int64_t)cfg->max_batch * cfg->num_kv_heads;
+    *whole = pairs > 256;
+    if (*whole && max_splits < 16)
+        return st;
+    const int fine = pairs <= 128 ? 512 : pairs <= 256 ? 1024 : 2048;
+    return fine < st ? fine : st;
+}
+
 // Token-major pools with at least two kv heads per work-group take the
 // head-parallel units (MFMA scores only) when the handle's full-capacity
 // batch, cut into four-wavefront units, would fit on the chip at once
@@ -1710,6 +1803,7 @@ struct rl_decode_attn {
     int split_tokens;
     int split_pages;
     int max_splits;
+    SplitRule rule;
     int device;
     bool use_mfma;
     bool head_parallel;
@@ -1819,6 +1913,11 @@ rl_da_status init_handle(rl_decode_attn* h, const rl_da_config* cfg)
     h->use_mfma = (cfg->flags & RL_DA_SCORES_ON_VALU) == 0;
     h->head_parallel = uses_head_parallel(cfg);
     h->heads_per_unit = h->head_parallel ? heads_per_unit_for(cfg->num_kv_heads) : 1;
+    h->rule.pages = sp;
+    h->rule.slots = ms;
+    bool whole;
+    h->rule.min_pages = min_split_tokens(cfg, st, ms, h->head_parallel, &whole) / kPageSize;
+    h->rule.whole = whole ? sp : 0;
     for (int persistent = 0; persistent < 2; ++persistent)
         (persistent ? h->split_kernel_persistent : h->split_kernel) = select_split_kernel(
             G, (cfg->flags & RL_DA_CHECKED) != 0, cfg->kv_dtype == RL_DA_KV_FP8_E4M3, h->use_mfma,
@@ -1905,7 +2004,9 @@ rl_da_status enqueue_run(rl_decode_attn* h, const void* q, const void* k_pool,
     if (batch == 0)
         return RL_DA_OK;
 
-    const int num_splits = (max_pages + h->split_pages - 1) / h->split_pages;
+    const int shortest = max_pages <= h->rule.whole ? h->rule.pages : h->rule.min_pages;
+    const int most = (max_pages + shortest - 1) / shortest;
+    const int num_splits = most < h->max_splits ? most : h->max_splits;
     const int64_t units = (int64_t)batch * (cfg.num_kv_heads / h->heads_per_unit) * num_splits;
     if (units + h->persistent_grid > INT32_MAX)
         return RL_DA_ERR_UNSUPPORTED;
@@ -1945,7 +2046,7 @@ rl_da_status enqueue_run(rl_decode_attn* h, const void* q, const void* k_pool,
     sa.num_q_heads = cfg.num_q_heads;
     sa.num_kv_heads = cfg.num_kv_heads;
     sa.max_pages = max_pages;
-    sa.split_pages = h->split_pages;
+    sa.rule = h->rule;
     sa.num_splits = num_splits;
     sa.heads_per_unit = h->heads_per_unit;
     sa.batch = batch;
@@ -1981,9 +2082,11 @@ rl_da_status enqueue_run(rl_decode_attn* h, const void* q, const void* k_pool,
         ma.out = (uint16_t*)out;
         ma.num_q_heads = cfg.num_q_heads;
         ma.max_pages = max_pages;
-        ma.split_pages = h->split_pages;
+        ma.rule = h->rule;
         ma.num_splits = num_splits;
-        hipLaunchKernelGGL(merge_splits, dim3((unsigned)((int64_t)batch * cfg.num_q_heads)),
+        ma.rows = merge_rows(batch, cfg.num_q_heads);
+        hipLaunchKernelGGL(merge_splits,
+                           dim3((unsigned)((int64_t)batch * cfg.num_q_heads / ma.rows)),
                            dim3(kWave * kMergeWaves), 0, st, ma);
         if (hipGetLastError() != hipSuccess)
             return RL_DA_ERR_HIP;

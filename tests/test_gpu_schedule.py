@@ -148,3 +148,31 @@ def test_queue_is_reset_between_launches_of_any_shape():
     finally:
         for h in handles.values():
             h.close()
+
+
+@pytest.mark.parametrize("kv,layout", [("bf16", "hnd"), ("fp8_e4m3", "nhd")])
+@pytest.mark.parametrize("max_batch,lengths", [
+    # 2 kv heads: 512-token splits from the shortest up (16 splits at most)
+    (32, [0, 1, 511, 512, 513, 1025, 4095, 4096, 4097, 8191, 32768, 16, 0, 3000]),
+    # 1024-token splits
+    (100, [1024, 1025, 2049, 5, 9000, 32767]),
+    # 2048-token splits, sequences of up to 4096 tokens whole
+    (200, [4096, 4097, 2049, 6145, 0, 20000, 32768, 7]),
+])
+def test_default_splits_follow_the_sequence_length(max_batch, lengths, kv, layout):
+    """Handles with the default split size cut a sequence by its own length.
+    Every length at the edges of the rule against the oracle; a sequence's bits
+    alone, in a table just wide enough for it, are those of the whole batch."""
+    p = problem(8, 2, lengths, seed=101 + max_batch, kv=kv, layout=layout, max_pages=2048)
+    with B.DecodeAttention(8, 2, max_batch, 4096, kv_dtype=kv, layout=layout,
+                           flags=B.RL_DA_PER_HEAD_UNITS) as attn:
+        assert attn.unit_heads() == 1 and attn.split_info(4096) == (4096, 16)
+        got = run_gpu(p, attn=attn)
+        for b in (len(lengths) - 1, 4, 1):
+            one = sub_problem(p, [b])
+            one.block_table = one.block_table[:, :max(1, (lengths[b] + 15) // 16)].contiguous()
+            assert torch.equal(run_gpu(one, attn=attn).view(torch.int16),
+                               got[b:b + 1].view(torch.int16)), b
+    print(check_close(bf16_to_f64(got), oracle_ref(p), "by length %d %s" % (max_batch, kv),
+                      extra_abs=decode_extra(p, 0)))
+    assert np.all(bf16_to_f64(got)[np.array(lengths) == 0] == 0)
