@@ -249,6 +249,37 @@ rl_da_status rl_extend_attn(const void* q, const int32_t* q_start, int32_t max_q
                             void* out, void* stream);
 
 /*
+ * rl_extend_attn with a workspace in device memory.  rl_extend_attn walks each
+ * tile's keys in one work-group; with a workspace the keys of a sequence with
+ * few new tokens (at most 512 query rows per kv head) after a long history (at
+ * least 4096 cached tokens) are divided among up to eight work-groups, whose
+ * partial results a second kernel merges in a fixed order.  Which sequences are
+ * divided, and where, follows from each one's own lengths, so a sequence's output
+ * does not depend on the rest of the batch; it equals rl_extend_attn's within
+ * rounding.  The workspace is written and read by the launches of this call
+ * only: it needs no initial contents and may be reused or freed once the
+ * stream has passed them.  workspace NULL: as rl_extend_attn.
+ *
+ * rl_extend_attn_workspace_size stores the bytes a call with these sizes should
+ * bring: 0 when its table is too narrow for any sequence to be divided (any
+ * workspace is then ignored), else at most 512 MiB or what one sequence takes; a
+ * batch that would take more runs as several launches, and a smaller workspace
+ * of at least one sequence's share (batch 1) gives more launches and the same
+ * bits; below that share the call returns INVALID_ARG.  The workspace is
+ * 16-byte aligned.
+ */
+rl_da_status rl_extend_attn_workspace_size(int32_t max_q_per_seq, int32_t max_pages, int32_t batch,
+                                           int32_t num_q_heads, int32_t num_kv_heads,
+                                           size_t* bytes);
+rl_da_status rl_extend_attn_ws(const void* q, const int32_t* q_start, int32_t max_q_per_seq,
+                               const void* k_pool, const void* v_pool, const float* k_scale,
+                               const float* v_scale, int64_t num_pages, const int32_t* block_table,
+                               int32_t max_pages, const int32_t* seq_lens, int32_t batch,
+                               int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                               int32_t page_size, int32_t kv_dtype, int32_t layout, float scale,
+                               void* out, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * KV-cache append: the step before attention in every decode step (the
  * rollout engine generates one token per sequence per step, Sec. 2.1; the
  * new token's key and value join the paged cache the attention then reads).

@@ -49,6 +49,8 @@ EXPORTED = [
     "rl_decode_attn_split_info",
     "rl_decode_attn_unit_heads",
     "rl_extend_attn",
+    "rl_extend_attn_workspace_size",
+    "rl_extend_attn_ws",
     "rl_kv_append",
     "rl_decode_attn_set_timing_events",
     "rl_ws_plan",
@@ -145,6 +147,12 @@ def load_library():
     lib.rl_extend_attn.argtypes = [vp, vp, i32, vp, vp, vp, vp, i64, vp, i32, vp, i32, i32, i32,
                                    i32, i32, i32, i32, ctypes.c_float, vp, vp]
     lib.rl_extend_attn.restype = ctypes.c_int
+    lib.rl_extend_attn_ws.argtypes = (lib.rl_extend_attn.argtypes[:-1]
+                                      + [vp, ctypes.c_size_t, vp])
+    lib.rl_extend_attn_ws.restype = ctypes.c_int
+    lib.rl_extend_attn_workspace_size.argtypes = [i32, i32, i32, i32, i32,
+                                                  ctypes.POINTER(ctypes.c_size_t)]
+    lib.rl_extend_attn_workspace_size.restype = ctypes.c_int
     lib.rl_kv_append.argtypes = [vp, vp, vp, vp, vp, vp, i64, vp, i32, vp, i32, i32, i32, i32,
                                  i32, i32, vp, vp]
     lib.rl_kv_append.restype = ctypes.c_int
@@ -347,9 +355,60 @@ def rl_extend_attn(q, q_start, max_q_per_seq, k_pool, v_pool, k_scale, v_scale, 
         int(kv_dtype), int(layout), float(scale), _ptr(out), _stream(stream))
 
 
+def rl_extend_attn_workspace_size(max_q_per_seq, max_pages, batch, num_q_heads, num_kv_heads):
+    """Returns (status, bytes)."""
+    n = ctypes.c_size_t()
+    rc = load_library().rl_extend_attn_workspace_size(
+        int(max_q_per_seq), int(max_pages), int(batch), int(num_q_heads), int(num_kv_heads),
+        ctypes.byref(n))
+    return rc, n.value
+
+
+def rl_extend_attn_ws(q, q_start, max_q_per_seq, k_pool, v_pool, k_scale, v_scale, num_pages,
+                      block_table, max_pages, seq_lens, batch, num_q_heads, num_kv_heads,
+                      head_dim=128, page_size=16, kv_dtype=RL_DA_KV_BF16,
+                      layout=RL_DA_LAYOUT_HND, scale=1.0, out=None, workspace=None,
+                      workspace_bytes=0, stream=None) -> int:
+    return load_library().rl_extend_attn_ws(
+        _ptr(q), _ptr(q_start), int(max_q_per_seq), _ptr(k_pool), _ptr(v_pool), _ptr(k_scale),
+        _ptr(v_scale), int(num_pages), _ptr(block_table), int(max_pages), _ptr(seq_lens),
+        int(batch), int(num_q_heads), int(num_kv_heads), int(head_dim), int(page_size),
+        int(kv_dtype), int(layout), float(scale), _ptr(out), _ptr(workspace),
+        int(workspace_bytes), _stream(stream))
+
+
+def _stream_scratch(nbytes, device, stream):
+    """nbytes of torch's memory that belong to `stream`: torch's allocator gives
+    a block back to the stream it was allocated on, so it may be dropped as
+    soon as that stream's last use of it is enqueued."""
+    import torch
+    current = torch.cuda.current_stream(device)
+    handle = _stream(stream) or 0
+    if handle == current.cuda_stream:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    own = (torch.cuda.ExternalStream(handle, device=device) if handle
+           else torch.cuda.default_stream(device))
+    with torch.cuda.stream(own):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+# Launches of fewer work-groups than this divide long histories.  The device holds
+# 512 at once (256 CUs, two each), and the partial results cost about what a
+# nearly full launch gains: 288 (12 sequences of 5..90 new tokens after
+# 2000..16000, 8 kv heads) 342 -> 234 us, 446 (223 of 1..14 after 8669, 2 kv
+# heads) 314 -> 323 us, 512 (64 of 32 after 4096, 8 kv heads) 207 -> 252 us.
+_EXTEND_DIVIDES_BELOW = 384
+
+
 def extend_attention(p, q, q_start, max_q_per_seq, out, stream=None):
     """Extend attention of new tokens q [T, Hq, D] (rows q_start[b]..) over
-    problem p's cache (p.seq_lens include the new tokens); raises on error."""
+    problem p's cache (p.seq_lens include the new tokens); raises on error.
+    A launch that cannot fill the device brings a workspace of torch's memory,
+    so that long histories are divided (rl_extend_attn_ws); others do without
+    (rl_extend_attn), since the partial results cost more than they gain there.
+    A sequence of 4096 cached tokens or more may therefore differ in rounding
+    between a small and a large batch; either C function alone gives the same
+    bits in any."""
     import torch
     dt = RL_DA_KV_BF16 if p.kv_dtype == "bf16" else RL_DA_KV_FP8_E4M3
     dev = p.k_pool.device
@@ -361,10 +420,18 @@ def extend_attention(p, q, q_start, max_q_per_seq, out, stream=None):
                  layout=LAYOUTS[p.layout], num_kv_heads=p.num_kv_heads, head_dim=p.head_dim,
                  page_size=p.page_size, device=dev)
     _check_table(p.block_table, p.seq_lens, p.batch, dev)
-    rc = rl_extend_attn(q, q_start, max_q_per_seq, p.k_pool, p.v_pool, p.k_scale, p.v_scale,
-                        p.num_pages, p.block_table, p.max_pages, p.seq_lens, p.batch,
-                        p.num_q_heads, p.num_kv_heads, p.head_dim, p.page_size, dt,
-                        LAYOUTS[p.layout], p.scale, out, stream)
+    ws, nbytes = None, 0
+    # tiles of 128 query rows per kv head, as the kernel cuts them
+    tiles = -(-max_q_per_seq * (p.num_q_heads // p.num_kv_heads) // 128)
+    if p.batch * p.num_kv_heads * tiles < _EXTEND_DIVIDES_BELOW and p.max_pages >= 256:
+        _, nbytes = rl_extend_attn_workspace_size(max_q_per_seq, p.max_pages, p.batch,
+                                                  p.num_q_heads, p.num_kv_heads)
+        if nbytes:
+            ws = _stream_scratch(nbytes, dev, stream)
+    rc = rl_extend_attn_ws(q, q_start, max_q_per_seq, p.k_pool, p.v_pool, p.k_scale, p.v_scale,
+                           p.num_pages, p.block_table, p.max_pages, p.seq_lens, p.batch,
+                           p.num_q_heads, p.num_kv_heads, p.head_dim, p.page_size, dt,
+                           LAYOUTS[p.layout], p.scale, out, ws, nbytes, stream)
     if rc != RL_DA_OK:
         raise RLDecodeAttnError(rc, "rl_extend_attn")
 

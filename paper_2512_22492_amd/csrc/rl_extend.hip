@@ -209,14 +209,51 @@ struct ExtendArgs {
     int32_t num_kv_heads;
     int32_t max_pages;
     int32_t num_tiles;          // ceil(max_q_per_seq / tile tokens)
+    int32_t split_slots;        // most splits of a sequence (SPLIT kernels)
+    int32_t split_tiles;        // tiles of a sequence that may be split
+    float* partials;            // [B][Hkv][split_tiles][split_slots] PartialTiles
     float scale_log2;           // |scale| * log2(e)
     uint32_t q_sign;            // 0x80008000 for a negative scale: Q enters negated
+};
+
+// Splits over the keys (SPLIT kernels, which have a workspace).  A tile walks its
+// keys one stage after another, about 1.4 us a stage when its CU holds no other,
+// so a few new tokens after long histories are a handful of serial walks on
+// an idle chip (one sequence of 60 new tokens after 30000, 8 kv heads: 16
+// work-groups, 599 us).  Such a sequence's keys are cut into nsplit equal runs
+// of stages, each a work unit that leaves its rows' (m, l, O) in the workspace,
+// and merge_extend combines them in split order: 92 us; 12 sequences of 5..90
+// new tokens after 2000..16000 344 -> 239 us (21 of them the merge); 12 of 32
+// after 16000 365 -> 199 us, 4.0 TB/s.  1024 keys a split and 16 splits measured
+// 64, 248 and 209 us: more partials, more set-ups.
+// Whether and where a sequence is cut follows from its own lengths alone.  At most
+// kSplitRows query rows, so that the partials (1040 bytes written and read per
+// row and split, against 512 or 256 per key) stay below what its keys cost;
+// kSplitKeys keys a split, 32 stages against the 5-10 us of a unit's set-up and
+// ends.  A launch that fills the chip without them is better off with no
+// workspace (64 sequences of 32 new tokens after 4096: 207 us, 252 us cut).
+constexpr int kSplitRows = 512;
+constexpr int kSplitKeys = 2048;
+constexpr int kMaxExtendSplits = 8;
+
+__host__ __device__ __forceinline__ int extend_splits(int rows, int len)
+{
+    if (rows > kSplitRows || len < 2 * kSplitKeys)
+        return 1;
+    const int n = len / kSplitKeys;
+    return n < kMaxExtendSplits ? n : kMaxExtendSplits;
+}
+
+// One unit's rows in the workspace.
+struct PartialTile {
+    float acc[kTileRows][kHeadDim];
+    float2 ml[kTileRows];  // running max (log2 units), sum of weights
 };
 
 // FP8: e4m3 pools.  Codes are staged as exact bf16 (scale 1); a page's
 // k_scale multiplies its keys' scores and its v_scale the probabilities that
 // weight its values (l sums the unscaled probabilities), as in decode.
-template <int G, bool FP8>
+template <int G, bool FP8, bool SPLIT>
 __global__ __launch_bounds__(kWave * kUnitWaves)
 __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
 {
@@ -239,30 +276,37 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
     // eighth pair of the batch; pairs past the last whole eight follow in
     // grid order.  A pair's last tile (the one that sees the most keys) is
     // dealt first, so the shortest tiles fill the end of the launch.
+    // A pair's later splits follow its tiles.
     const int T = a.num_tiles;
+    const int U = SPLIT ? T + (a.split_slots - 1) * a.split_tiles : T;  // units of a pair
     const int g = blockIdx.x;
-    const int main_units = (int)(gridDim.x / T / 8) * 8 * T;
-    int bk, tile;
+    const int main_units = (int)(gridDim.x / U / 8) * 8 * U;
+    int bk, tile, split = 0;
     if (g < main_units) {
-        bk = (g / 8 / T) * 8 + g % 8;
-        tile = T - 1 - (g / 8) % T;
+        bk = (g / 8 / U) * 8 + g % 8;
+        tile = T - 1 - (g / 8) % U;
     } else {
-        bk = g / T;
-        tile = T - 1 - g % T;
+        bk = g / U;
+        tile = T - 1 - g % U;
+    }
+    if (SPLIT && tile < 0) {
+        split = 1 + (-1 - tile) / a.split_tiles;
+        tile = a.split_tiles - 1 - (-1 - tile) % a.split_tiles;
     }
     // Pairs are taken longest sequence first, so that the longest tiles do
     // not start last and set the end of the launch.
     const int kvh = bk % a.num_kv_heads;
     // (the K staging buffer is free until the first stage is staged)
     const int b = sequence_at_rank(a.seq_lens, a.max_pages * kPageSize,
-                                   (int)(gridDim.x / T / a.num_kv_heads), bk / a.num_kv_heads,
+                                   (int)(gridDim.x / U / a.num_kv_heads), bk / a.num_kv_heads,
                                    reinterpret_cast<uint8_t*>(&k_lds0[0][0]), (int)sizeof(k_lds0));
     const int q0 = a.q_start[b];
     // lengths clamped to what the table row can hold, new tokens to the length
     const int L = min(a.seq_lens[b], a.max_pages * kPageSize);
     const int n_new = min(a.q_start[b + 1] - q0, L);
     const int tok0 = tile * kTileTok;
-    if (tok0 >= n_new)
+    const int nsplit = SPLIT ? extend_splits(n_new * G, L) : 1;
+    if (tok0 >= n_new || (SPLIT && split >= nsplit))
         return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
@@ -272,7 +316,15 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
 
     const int tile_last = min(tok0 + kTileTok, n_new) - 1;
     const int nkeys = base_pos + tile_last + 1;           // keys the tile sees
-    const int nstages = (nkeys + kStageKeys - 1) / kStageKeys;
+    // The unit's stages.  A sequence's last split holds its last run of more
+    // than kSplitRows + kStageKeys keys, so every split holds a key that each
+    // row of the tile sees, and only the last meets the causal diagonal.
+    const int per_split =
+        SPLIT ? ((L + kStageKeys - 1) / kStageKeys + nsplit - 1) / nsplit : 0;
+    const int first_stage = SPLIT ? split * per_split : 0;
+    const int tile_stages = (nkeys + kStageKeys - 1) / kStageKeys;
+    const int nstages =
+        SPLIT && nsplit > 1 ? min(tile_stages, first_stage + per_split) : tile_stages;
     const int first_masked_stage = (base_pos + tok0) / kStageKeys;
 
     float m_run[kRowBlocks], lsum[kRowBlocks];
@@ -447,12 +499,12 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
         voff_t[db] = (v_xor ^ (32 * db)) + v_lane;
         asm volatile("" : "+v"(voff_t[db]));
     }
-    stage_pages(0, pages_next);
+    stage_pages(first_stage, pages_next);
     if constexpr (FP8)
-        fetch(0, pages_next);
+        fetch(first_stage, pages_next);
     else
-        dma(0, pages_next, 0);
-    stage_pages(1, pages_next);
+        dma(first_stage, pages_next, first_stage & 1);
+    stage_pages(first_stage + 1, pages_next);
     // Q^T operand and the causal limit of this lane's row in each block,
     // read after the first stage's loads are issued (loads complete in order,
     // so the table reads those loads need wait for nothing else).  The eight
@@ -786,7 +838,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
         }
         __builtin_amdgcn_s_setprio(0);
     };
-    int j = 0;
+    int j = first_stage;
     auto run = [&](int end, auto masked_t) {
         for (; j < end; ++j)
             stage(j, masked_t, j & 1);
@@ -794,6 +846,28 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
     run(min(first_masked_stage, nstages), std::false_type{});
     run(nstages, std::true_type{});
 
+    if (SPLIT && nsplit > 1) {  // this split's rows, for merge_extend
+        PartialTile& part =
+            reinterpret_cast<PartialTile*>(a.partials)[(((int64_t)b * a.num_kv_heads + kvh) *
+                                                            a.split_tiles + tile) *
+                                                           a.split_slots + split];
+#pragma unroll
+        for (int rb = 0; rb < kRowBlocks; ++rb) {
+            const float l = FP8 ? sum_lanes_xor32(sum_lanes_xor16(lsum[rb])) : lacc[rb][0];
+            if (!row_real[rb])
+                continue;
+            const int r = wave * (kRowBlocks * 16) + rb * 16 + i16;
+#pragma unroll
+            for (int db = 0; db < 8; ++db) {
+                const floatx4_t& v = o[rb][db];
+                *reinterpret_cast<float4*>(&part.acc[r][16 * db + 4 * g4]) =
+                    make_float4(v[0], v[1], v[2], v[3]);
+            }
+            if (g4 == 0)
+                part.ml[r] = make_float2(m_run[rb], l);
+        }
+        return;
+    }
     // out[row] = O[row] / l[row]; lane holds row i16, dims 16db + 4g4 + jj.
 #pragma unroll
     for (int rb = 0; rb < kRowBlocks; ++rb) {
@@ -814,6 +888,119 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
     }
 }
 
+// ------------------------------------------------- merge of the splits ---
+//
+// One work-group of four wavefronts per 32 rows of a tile that may be split:
+// out = sum_s w_s O_s / sum_s w_s l_s, w_s = 2^(m_s - max m), in split order, a
+// wavefront per row (two dims per lane).  A tile of an uncut sequence is
+// finished already, and its work-groups leave.
+
+constexpr int kMergeRows = 32;
+
+struct ExtendMergeArgs {
+    const int32_t* q_start;
+    const int32_t* seq_lens;
+    const float* partials;
+    uint16_t* out;
+    int32_t group;          // query heads per kv head
+    int32_t num_q_heads;
+    int32_t num_kv_heads;
+    int32_t max_pages;
+    int32_t split_slots;
+    int32_t split_tiles;
+};
+
+__global__ __launch_bounds__(kWave * kUnitWaves) void merge_extend(ExtendMergeArgs a)
+{
+    constexpr int kParts = kTileRows / kMergeRows;
+    const int at = blockIdx.x / kParts;
+    const int tile = at % a.split_tiles;
+    const int pair = at / a.split_tiles;
+    const int b = pair / a.num_kv_heads, kvh = pair % a.num_kv_heads;
+    const int q0 = a.q_start[b];
+    const int L = min(a.seq_lens[b], a.max_pages * kPageSize);
+    const int rows = min(a.q_start[b + 1] - q0, L) * a.group;  // of the sequence
+    const int n = extend_splits(rows, L);
+    const int first = (int)(blockIdx.x % kParts) * kMergeRows;
+    if (n < 2 || tile * kTileRows + first >= rows)
+        return;
+    const PartialTile* part =
+        reinterpret_cast<const PartialTile*>(a.partials) + (int64_t)at * a.split_slots;
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+#pragma unroll 2
+    for (int i = wave; i < kMergeRows; i += kUnitWaves) {
+        const int r = first + i, row = tile * kTileRows + r;
+        if (row >= rows)
+            break;
+        float2 ml[kMaxExtendSplits], v[kMaxExtendSplits];
+        float M = -INFINITY;
+#pragma unroll
+        for (int s = 0; s < kMaxExtendSplits; ++s) {
+            ml[s] = make_float2(-INFINITY, 0.0f);
+            v[s] = make_float2(0.0f, 0.0f);
+            if (s < n) {
+                ml[s] = part[s].ml[r];
+                v[s] = *reinterpret_cast<const float2*>(&part[s].acc[r][2 * lane]);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kMaxExtendSplits; ++s)
+            M = fmaxf(M, ml[s].x);
+        float den = 0.0f, x0 = 0.0f, x1 = 0.0f;
+#pragma unroll
+        for (int s = 0; s < kMaxExtendSplits; ++s) {
+            const float w = exp2_fast(ml[s].x - M);  // 0 past the last split
+            den = fmaf(w, ml[s].y, den);
+            x0 = fmaf(w, v[s].x, x0);
+            x1 = fmaf(w, v[s].y, x1);
+        }
+        const float inv = 1.0f / den;
+        const int64_t orow = (int64_t)(q0 + row / a.group) * a.num_q_heads + kvh * a.group +
+                             row % a.group;
+        *reinterpret_cast<uint32_t*>(a.out + orow * kHeadDim + 2 * lane) =
+            f32_to_bf16(x0 * inv) | (f32_to_bf16(x1 * inv) << 16);
+    }
+}
+
+typedef void (*ExtendKernel)(ExtendArgs);
+
+template <bool FP8, bool SPLIT>
+ExtendKernel extend_kernel(int G)
+{
+    switch (G) {
+    case 1: return extend_attn<1, FP8, SPLIT>;
+    case 2: return extend_attn<2, FP8, SPLIT>;
+    case 4: return extend_attn<4, FP8, SPLIT>;
+    case 8: return extend_attn<8, FP8, SPLIT>;
+    default: return extend_attn<16, FP8, SPLIT>;
+    }
+}
+
+// Tiles of one sequence and kv head that may be split, the splits of the
+// longest sequence the table holds, and the workspace that they take.
+struct ExtendSplitShape {
+    int tiles, slots;
+    int64_t bytes_per_seq;  // 0: nothing is split
+};
+
+ExtendSplitShape extend_split_shape(int32_t max_q_per_seq, int32_t max_pages, int32_t num_kv_heads,
+                                    int G)
+{
+    const int64_t rows = (int64_t)max_q_per_seq * G;
+    const int64_t tiles = (rows + kTileRows - 1) / kTileRows;
+    ExtendSplitShape s;
+    s.tiles = (int)(tiles < kSplitRows / kTileRows ? tiles : kSplitRows / kTileRows);
+    const int64_t keys = (int64_t)max_pages * kPageSize;
+    s.slots = extend_splits(1, (int)(keys < INT32_MAX ? keys : INT32_MAX));
+    s.bytes_per_seq =
+        s.slots > 1 ? (int64_t)num_kv_heads * s.tiles * s.slots * (int64_t)sizeof(PartialTile) : 0;
+    return s;
+}
+
+// A batch whose partials would take more than this runs as several launches
+// that share the workspace one after another.
+constexpr int64_t kExtendWorkspaceLimit = (int64_t)1 << 29;
+
 }  // namespace
 
 extern "C" {
@@ -825,6 +1012,35 @@ rl_da_status rl_extend_attn(const void* q, const int32_t* q_start, int32_t max_q
                             int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
                             int32_t page_size, int32_t kv_dtype, int32_t layout, float scale,
                             void* out, void* stream)
+{
+    return rl_extend_attn_ws(q, q_start, max_q_per_seq, k_pool, v_pool, k_scale, v_scale, num_pages,
+                             block_table, max_pages, seq_lens, batch, num_q_heads, num_kv_heads,
+                             head_dim, page_size, kv_dtype, layout, scale, out, nullptr, 0, stream);
+}
+
+rl_da_status rl_extend_attn_workspace_size(int32_t max_q_per_seq, int32_t max_pages, int32_t batch,
+                                           int32_t num_q_heads, int32_t num_kv_heads, size_t* bytes)
+{
+    if (bytes == nullptr || max_q_per_seq < 0 || max_pages < 1 || batch < 0 || num_q_heads <= 0 ||
+        num_kv_heads <= 0 || num_q_heads % num_kv_heads != 0)
+        return RL_DA_ERR_INVALID_ARG;
+    const ExtendSplitShape s =
+        extend_split_shape(max_q_per_seq, max_pages, num_kv_heads, num_q_heads / num_kv_heads);
+    int64_t seqs = batch;
+    if (s.bytes_per_seq > 0 && seqs * s.bytes_per_seq > kExtendWorkspaceLimit)
+        seqs = kExtendWorkspaceLimit / s.bytes_per_seq > 1 ? kExtendWorkspaceLimit / s.bytes_per_seq
+                                                           : 1;
+    *bytes = (size_t)(seqs * s.bytes_per_seq);
+    return RL_DA_OK;
+}
+
+rl_da_status rl_extend_attn_ws(const void* q, const int32_t* q_start, int32_t max_q_per_seq,
+                               const void* k_pool, const void* v_pool, const float* k_scale,
+                               const float* v_scale, int64_t num_pages, const int32_t* block_table,
+                               int32_t max_pages, const int32_t* seq_lens, int32_t batch,
+                               int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                               int32_t page_size, int32_t kv_dtype, int32_t layout, float scale,
+                               void* out, void* workspace, size_t workspace_bytes, void* stream)
 {
     if (q == nullptr || q_start == nullptr || k_pool == nullptr || v_pool == nullptr ||
         block_table == nullptr || seq_lens == nullptr || out == nullptr)
@@ -873,22 +1089,62 @@ rl_da_status rl_extend_attn(const void* q, const int32_t* q_start, int32_t max_q
     ea.num_tiles = (max_q_per_seq + tile_tok - 1) / tile_tok;
     ea.scale_log2 = fabsf(scale) * kLog2e;
     ea.q_sign = scale < 0.0f ? 0x80008000u : 0u;
-    const int64_t blocks = (int64_t)batch * num_kv_heads * ea.num_tiles;
-    if (blocks > INT32_MAX)
-        return RL_DA_ERR_UNSUPPORTED;
-    hipStream_t st = (hipStream_t)stream;
-    const dim3 grid((unsigned)blocks), block(kWave * kUnitWaves);
-    typedef void (*Kernel)(ExtendArgs);
-    Kernel k;
-    switch (G) {
-    case 1: k = fp8 ? extend_attn<1, true> : extend_attn<1, false>; break;
-    case 2: k = fp8 ? extend_attn<2, true> : extend_attn<2, false>; break;
-    case 4: k = fp8 ? extend_attn<4, true> : extend_attn<4, false>; break;
-    case 8: k = fp8 ? extend_attn<8, true> : extend_attn<8, false>; break;
-    default: k = fp8 ? extend_attn<16, true> : extend_attn<16, false>; break;
+    // With a workspace, sequences are taken `seqs` at a time.
+    int32_t seqs = batch;
+    ExtendSplitShape ss = {0, 1, 0};
+    if (workspace != nullptr)
+        ss = extend_split_shape(max_q_per_seq, max_pages, num_kv_heads, G);
+    const bool split = ss.bytes_per_seq > 0;
+    if (split) {
+        const uint64_t fit = workspace_bytes / (uint64_t)ss.bytes_per_seq;
+        if (fit < 1 || !aligned16(workspace))
+            return RL_DA_ERR_INVALID_ARG;
+        seqs = fit < (uint64_t)batch ? (int32_t)fit : batch;
     }
-    hipLaunchKernelGGL(k, grid, block, 0, st, ea);
-    return hipGetLastError() == hipSuccess ? RL_DA_OK : RL_DA_ERR_HIP;
+    ea.split_slots = ss.slots;
+    ea.split_tiles = ss.tiles;
+    ea.partials = (float*)workspace;
+    if ((int64_t)batch * num_kv_heads * ea.num_tiles > INT32_MAX)
+        return RL_DA_ERR_UNSUPPORTED;
+    const int64_t units = ea.num_tiles + (int64_t)(ss.slots - 1) * ss.tiles;  // of a pair
+    const int64_t grid_seqs = INT32_MAX / (units * num_kv_heads);  // that one grid can take
+    if (grid_seqs < 1)
+        return RL_DA_ERR_UNSUPPORTED;
+    if (seqs > grid_seqs)
+        seqs = (int32_t)grid_seqs;
+    hipStream_t st = (hipStream_t)stream;
+    const dim3 block(kWave * kUnitWaves);
+    const ExtendKernel k = split ? (fp8 ? extend_kernel<true, true>(G) : extend_kernel<false, true>(G))
+                                 : (fp8 ? extend_kernel<true, false>(G) : extend_kernel<false, false>(G));
+    for (int32_t b0 = 0; b0 < batch; b0 += seqs) {
+        const int32_t nb = batch - b0 < seqs ? batch - b0 : seqs;
+        ea.q_start = q_start + b0;
+        ea.seq_lens = seq_lens + b0;
+        ea.block_table = block_table + (int64_t)b0 * max_pages;
+        hipLaunchKernelGGL(k, dim3((unsigned)(nb * num_kv_heads * units)), block, 0, st, ea);
+        if (hipGetLastError() != hipSuccess)
+            return RL_DA_ERR_HIP;
+        if (!split)
+            continue;
+        ExtendMergeArgs ma;
+        ma.q_start = ea.q_start;
+        ma.seq_lens = ea.seq_lens;
+        ma.partials = ea.partials;
+        ma.out = ea.out;
+        ma.group = G;
+        ma.num_q_heads = num_q_heads;
+        ma.num_kv_heads = num_kv_heads;
+        ma.max_pages = max_pages;
+        ma.split_slots = ss.slots;
+        ma.split_tiles = ss.tiles;
+        hipLaunchKernelGGL(merge_extend,
+                           dim3((unsigned)((int64_t)nb * num_kv_heads * ss.tiles *
+                                           (kTileRows / kMergeRows))),
+                           block, 0, st, ma);
+        if (hipGetLastError() != hipSuccess)
+            return RL_DA_ERR_HIP;
+    }
+    return RL_DA_OK;
 }
 
 }  // extern "C"

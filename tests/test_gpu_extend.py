@@ -341,3 +341,53 @@ def test_extend_rows_do_not_depend_on_the_rest_of_the_batch(kv):
             assert torch.equal(got[at:at + n].view(torch.int16),
                                full[starts[b]:starts[b] + n].view(torch.int16)), (rows, b)
             at += n
+
+
+# A sequence is divided over its keys from 4096 cached tokens on, if its new
+# tokens' rows (per kv head) number 512 at most; 2048 keys a split, 8 splits at most.
+SPLIT_CASES = [
+    # hq, hkv, new, prior
+    (8, 2, [1, 128, 129, 33, 0, 5], [4095, 3968, 4200, 4062, 5000, 6139]),
+    (4, 4, [512, 513, 3], [3584, 4000, 8190]),
+    (16, 1, [32, 33, 7], [4096, 6200, 17000]),
+]
+
+
+@pytest.mark.parametrize("kv,layout", [("bf16", "hnd"), ("fp8_e4m3", "nhd")])
+@pytest.mark.parametrize("case", range(len(SPLIT_CASES)))
+def test_extend_divided_over_keys(case, kv, layout):
+    """Sequences on both sides of the rule against the oracle; the same bits
+    alone, in a wider table, and with a workspace of one sequence's share (one launch
+    a sequence); rl_extend_attn without a workspace agrees within the same
+    bound."""
+    hq, hkv, new, prior = SPLIT_CASES[case]
+    print("case", case, kv, layout, flush=True)
+    p, q, q_start = extend_problem(new, prior, seed=61 + case, hq=hq, hkv=hkv, kv=kv,
+                                   layout=layout)
+    got = run_extend(p, q, q_start, max(new))
+    check_extend(p, q, q_start, got, "divided %d %s" % (case, kv))
+    dt = B.KV_DTYPES[kv]
+
+    def call(fn, **kw):
+        out = torch.full_like(q, float("nan"))
+        assert fn(q, q_start, max(new), p.k_pool, p.v_pool, p.k_scale, p.v_scale, p.num_pages,
+                  p.block_table, p.max_pages, p.seq_lens, p.batch, hq, hkv, kv_dtype=dt,
+                  layout=B.LAYOUTS[layout], scale=p.scale, out=out, **kw) == B.RL_DA_OK
+        torch.cuda.synchronize()
+        return out
+
+    rc, share = B.rl_extend_attn_workspace_size(max(new), p.max_pages, 1, hq, hkv)
+    assert rc == B.RL_DA_OK and share > 0
+    # every byte starts as a NaN, and what lies behind the share is left alone
+    ws = torch.full((share + 256,), 0xff, dtype=torch.uint8, device=device())
+    small = call(B.rl_extend_attn_ws, workspace=ws, workspace_bytes=share)
+    assert torch.equal(small.view(torch.int16), got.view(torch.int16))
+    assert torch.all(ws[share:] == 0xff)
+    check_extend(p, q, q_start, call(B.rl_extend_attn), "undivided %d %s" % (case, kv))
+    b = 0
+    wide = torch.zeros((1, 4096), dtype=torch.int32, device=device())
+    wide[:, :p.max_pages] = p.block_table[b:b + 1]
+    sub = workloads.DecodeProblem(**{**p.__dict__, "batch": 1, "block_table": wide,
+                                     "seq_lens": p.seq_lens[b:b + 1].contiguous()})
+    alone = run_extend(sub, q[:new[b]].contiguous(), q_start[:2].contiguous(), new[b])
+    assert torch.equal(alone.view(torch.int16), got[:new[b]].view(torch.int16))
