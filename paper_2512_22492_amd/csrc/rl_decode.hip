@@ -1750,26 +1750,24 @@ int default_split_tokens(const rl_da_config* cfg, int64_t units_per_split)
 // length (357 MB).  The line, from sweeps of the split size on one box:
 //   * up to 128 pairs of (sequence, kv head) even a full batch leaves CUs
 //     idle unless it is cut: 512 (64 x 1 pairs, lengths around 4096: 73.6 us at
-//     4096, 52.3 at 2048, 47.7 at 1024, 44.0 at 512, 44.9 at 256); up to 256
-//     pairs 1024;
+//     4096, 52.3 at 2048, 47.7 at 1024, 44.0 at 512, 44.9 at 256);
 //   * above that a full batch fills the chip and every cut costs it (64 x 8 pairs
 //     of 4096 tokens: 180.3 us whole, 184.1 at 2048, 196.3 at 512), so only
 //     sequences longer than one default split are cut, to 2048 at least;
 //   * and only where the table holds 16 default splits: in one made for its
 //     batch's longest sequence those above half its width take longer splits
 //     than the others and end the launch (128 x 4 pairs, lognormal to 32768
-//     in a table of 32768: 286 us whole, 311 us cut).
+//     in a table of 32768: 286 us whole, 311 us cut; 173 x 1 pairs of
+//     4k..22k tokens in a table of 22k: 227 us whole, 250 us cut).
 int min_split_tokens(const rl_da_config* cfg, int st, int max_splits, bool head_parallel,
                      bool* whole)
 {
     *whole = true;
-    if (cfg->split_tokens != 0 || max_splits == 1 || head_parallel)
+    if (cfg->split_tokens != 0 || max_splits < 16 || head_parallel)
         return st;
     const int64_t pairs = (int64_t)cfg->max_batch * cfg->num_kv_heads;
-    *whole = pairs > 256;
-    if (*whole && max_splits < 16)
-        return st;
-    const int fine = pairs <= 128 ? 512 : pairs <= 256 ? 1024 : 2048;
+    *whole = pairs > 128;
+    const int fine = *whole ? 2048 : 512;
     return fine < st ? fine : st;
 }
 
