@@ -251,14 +251,17 @@ rl_da_status rl_extend_attn(const void* q, const int32_t* q_start, int32_t max_q
 /*
  * rl_extend_attn with a workspace in device memory.  rl_extend_attn walks each
  * tile's keys in one work-group; with a workspace the keys of a sequence with
- * few new tokens (at most 512 query rows per kv head) after a long history (at
- * least 4096 cached tokens) are divided among up to eight work-groups, whose
- * partial results a second kernel merges in a fixed order.  Which sequences are
+ * few new tokens (at most 512 query rows per kv head) and a long history (at
+ * least 4096 cached tokens, the new ones among them) are divided among up to eight
+ * work-groups, whose partial results a second kernel merges in a fixed order.  Which sequences are
  * divided, and where, follows from each one's own lengths, so a sequence's output
  * does not depend on the rest of the batch; it equals rl_extend_attn's within
  * rounding.  The workspace is written and read by the launches of this call
  * only: it needs no initial contents and may be reused or freed once the
- * stream has passed them.  workspace NULL: as rl_extend_attn.
+ * stream has passed them.  workspace NULL: as rl_extend_attn.  It pays where the
+ * launch leaves the device idle (fewer than 384 tiles of 128 query rows and
+ * kv head) and histories are long: the grid holds the splits of a sequence that
+ * fills the table, and a second launch follows.
  *
  * rl_extend_attn_workspace_size stores the bytes a call with these sizes should
  * bring: 0 when its table is too narrow for any sequence to be divided (any

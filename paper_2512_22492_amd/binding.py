@@ -377,38 +377,21 @@ def rl_extend_attn_ws(q, q_start, max_q_per_seq, k_pool, v_pool, k_scale, v_scal
         int(workspace_bytes), _stream(stream))
 
 
-def _stream_scratch(nbytes, device, stream):
-    """nbytes of torch's memory that belong to `stream`: torch's allocator gives
-    a block back to the stream it was allocated on, so it may be dropped as
-    soon as that stream's last use of it is enqueued."""
-    import torch
-    current = torch.cuda.current_stream(device)
-    handle = _stream(stream) or 0
-    if handle == current.cuda_stream:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
-    own = (torch.cuda.ExternalStream(handle, device=device) if handle
-           else torch.cuda.default_stream(device))
-    with torch.cuda.stream(own):
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
-
-
-# Launches of fewer work-groups than this divide long histories.  The device holds
-# 512 at once (256 CUs, two each), and the partial results cost about what a
-# nearly full launch gains: 288 (12 sequences of 5..90 new tokens after
-# 2000..16000, 8 kv heads) 342 -> 234 us, 446 (223 of 1..14 after 8669, 2 kv
-# heads) 314 -> 323 us, 512 (64 of 32 after 4096, 8 kv heads) 207 -> 252 us.
-_EXTEND_DIVIDES_BELOW = 384
-
-
-def extend_attention(p, q, q_start, max_q_per_seq, out, stream=None):
+def extend_attention(p, q, q_start, max_q_per_seq, out, stream=None, workspace=None):
     """Extend attention of new tokens q [T, Hq, D] (rows q_start[b]..) over
     problem p's cache (p.seq_lens include the new tokens); raises on error.
-    A launch that cannot fill the device brings a workspace of torch's memory,
-    so that long histories are divided (rl_extend_attn_ws); others do without
-    (rl_extend_attn), since the partial results cost more than they gain there.
-    A sequence of 4096 cached tokens or more may therefore differ in rounding
-    between a small and a large batch; either C function alone gives the same
-    bits in any."""
+
+    workspace: a contiguous uint8 tensor of rl_extend_attn_workspace_size bytes that
+    the caller keeps, for launches that leave the device idle (a few new tokens
+    after long histories): rl_extend_attn_ws then divides long histories among
+    work-groups.  One launch uses it at a time, so streams that overlap bring one
+    each.  A sequence's output has the same bits in any batch and table either
+    way; with a workspace it differs in rounding from without.  Launches of 384
+    work-groups and more (batch * kv heads * tiles of 128 query rows) are better
+    off without: 288 (12 sequences of 5..90 new tokens after 2000..16000, 8 kv
+    heads) 342 -> 234 us, 446 (223 of 1..14 after 8669, 2 kv heads) 314 -> 323 us,
+    512 (64 of 32 after 4096, 8 kv heads) 207 -> 252 us; and so are launches whose
+    histories are short, since the grid follows the table's width."""
     import torch
     dt = RL_DA_KV_BF16 if p.kv_dtype == "bf16" else RL_DA_KV_FP8_E4M3
     dev = p.k_pool.device
@@ -420,18 +403,14 @@ def extend_attention(p, q, q_start, max_q_per_seq, out, stream=None):
                  layout=LAYOUTS[p.layout], num_kv_heads=p.num_kv_heads, head_dim=p.head_dim,
                  page_size=p.page_size, device=dev)
     _check_table(p.block_table, p.seq_lens, p.batch, dev)
-    ws, nbytes = None, 0
-    # tiles of 128 query rows per kv head, as the kernel cuts them
-    tiles = -(-max_q_per_seq * (p.num_q_heads // p.num_kv_heads) // 128)
-    if p.batch * p.num_kv_heads * tiles < _EXTEND_DIVIDES_BELOW and p.max_pages >= 256:
-        _, nbytes = rl_extend_attn_workspace_size(max_q_per_seq, p.max_pages, p.batch,
-                                                  p.num_q_heads, p.num_kv_heads)
-        if nbytes:
-            ws = _stream_scratch(nbytes, dev, stream)
+    nbytes = 0
+    if workspace is not None:
+        _check_tensor("workspace", workspace, dtype=torch.uint8, ndim=1, device=dev)
+        nbytes = int(workspace.shape[0])
     rc = rl_extend_attn_ws(q, q_start, max_q_per_seq, p.k_pool, p.v_pool, p.k_scale, p.v_scale,
                            p.num_pages, p.block_table, p.max_pages, p.seq_lens, p.batch,
                            p.num_q_heads, p.num_kv_heads, p.head_dim, p.page_size, dt,
-                           LAYOUTS[p.layout], p.scale, out, ws, nbytes, stream)
+                           LAYOUTS[p.layout], p.scale, out, workspace, nbytes, stream)
     if rc != RL_DA_OK:
         raise RLDecodeAttnError(rc, "rl_extend_attn")
 

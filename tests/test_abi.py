@@ -202,6 +202,50 @@ def test_extend_host_checks_without_gpu():
                     layout=layout) == B.RL_DA_ERR_UNSUPPORTED
 
 
+def test_extend_workspace_host_checks_without_gpu():
+    """rl_extend_attn_ws refuses a workspace that is misaligned or smaller than one
+    sequence's share before touching the device; the size is 0 where no
+    sequence can be divided, and one share at least, 512 MiB at most else."""
+    def size(max_q=64, max_pages=4096, batch=12, hq=32, hkv=8):
+        rc, n = B.rl_extend_attn_workspace_size(max_q, max_pages, batch, hq, hkv)
+        assert rc == B.RL_DA_OK
+        return n
+
+    # 2 tiles x 8 splits x 8 kv heads of 128 rows: fp32 sums, (max, weight sum)
+    share = 2 * 8 * 8 * 128 * (128 + 2) * 4
+    assert size(batch=1) == share and size() == 12 * share
+    assert size(max_pages=255) == 0                      # 4080 tokens: nothing is divided
+    assert size(max_pages=256, batch=1) == share // 4    # two splits
+    assert size(max_q=0) == 0 and size(batch=0) == 0
+    limit = 1 << 29
+    assert size(batch=1000) == limit // share * share
+    wide = size(max_q=512, batch=1, hq=1024, hkv=1024)   # a share beyond the limit
+    assert wide > limit and size(max_q=512, batch=9, hq=1024, hkv=1024) == wide
+    for bad in (dict(max_q=-1), dict(max_pages=0), dict(batch=-1), dict(hq=0), dict(hkv=0),
+                dict(hq=12)):
+        kw = dict(max_q=64, max_pages=4096, batch=12, hq=32, hkv=8)
+        kw.update(bad)
+        assert B.rl_extend_attn_workspace_size(*kw.values())[0] == B.RL_DA_ERR_INVALID_ARG
+    lib = B.load_library()
+    assert lib.rl_extend_attn_workspace_size(64, 4096, 12, 32, 8, None) == B.RL_DA_ERR_INVALID_ARG
+
+    fake = 1 << 20
+
+    def call(**kw):
+        args = dict(q=fake, q_start=fake, max_q_per_seq=64, k_pool=fake, v_pool=fake,
+                    k_scale=None, v_scale=None, num_pages=16, block_table=fake, max_pages=4096,
+                    seq_lens=fake, batch=2, num_q_heads=32, num_kv_heads=8, out=fake,
+                    workspace=fake, workspace_bytes=2 * share)
+        args.update(kw)
+        return B.rl_extend_attn_ws(**args)
+
+    assert call(workspace_bytes=share - 1) == B.RL_DA_ERR_INVALID_ARG
+    assert call(workspace_bytes=0) == B.RL_DA_ERR_INVALID_ARG
+    assert call(workspace=fake + 8) == B.RL_DA_ERR_INVALID_ARG
+    assert call(q=None) == B.RL_DA_ERR_INVALID_ARG
+    assert call(batch=0) == B.RL_DA_OK and call(max_q_per_seq=0) == B.RL_DA_OK
+
+
 def test_kv_append_host_checks_without_gpu():
     """rl_kv_append refuses bad requests before touching the device (null or
     misaligned pointers, scales given exactly for e4m3 pools, shapes it has no

@@ -1,6 +1,8 @@
 """The binding's argument checks (CPU): what every entry point runs on each
 tensor before its C call, so a wrong dtype, shape, layout or device raises
 ValueError instead of reaching a kernel."""
+import types
+
 import pytest
 import torch
 
@@ -66,3 +68,33 @@ def test_check_table_and_pools():
         B._check_pools(k8, k8.clone(), None, None, **kw8)
     with pytest.raises(ValueError):
         B._check_pools(k8, k8.clone(), torch.ones((6, 3)), torch.ones((6, 2)), **kw8)
+
+
+def test_extend_divides_only_with_the_callers_workspace(monkeypatch):
+    """extend_attention brings no workspace of its own, whatever the launch's size
+    and table: what a sequence's rows are does not depend on the batch, the call
+    allocates nothing, and the caller's workspace goes through with its size."""
+    seen = []
+    monkeypatch.setattr(B, "rl_extend_attn_ws",
+                        lambda *a: seen.append((a[-3], a[-2])) or B.RL_DA_OK)
+
+    def call(batch, pages, new, workspace=None):
+        pool = torch.zeros((8, 2, 16, 128), dtype=torch.bfloat16)
+        p = types.SimpleNamespace(
+            kv_dtype="bf16", layout="hnd", num_q_heads=8, num_kv_heads=2, head_dim=128,
+            page_size=16, batch=batch, num_pages=8, max_pages=pages, scale=1.0, k_pool=pool,
+            v_pool=pool.clone(), k_scale=None, v_scale=None,
+            block_table=torch.zeros((batch, pages), dtype=torch.int32),
+            seq_lens=torch.ones(batch, dtype=torch.int32))
+        q = torch.zeros((batch * new, 8, 128), dtype=torch.bfloat16)
+        start = torch.arange(batch + 1, dtype=torch.int32) * new
+        B.extend_attention(p, q, start, new, torch.empty_like(q), None, workspace)
+        return seen.pop()
+
+    for batch, pages, new in ((1, 4096, 3), (1, 4, 3), (300, 4096, 1), (2, 4096, 300)):
+        assert call(batch, pages, new) == (None, 0)
+    ws = torch.zeros(1 << 20, dtype=torch.uint8)
+    assert call(1, 4096, 3, ws) == (ws, 1 << 20)
+    for bad in (ws.view(torch.int32), ws[::2], ws.view(2, -1), 7):
+        with pytest.raises(ValueError):
+            call(1, 4096, 3, bad)

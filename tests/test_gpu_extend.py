@@ -26,11 +26,19 @@ def extend_problem(new, prior, seed, hq=8, hkv=2, layout="hnd", kv="bf16"):
     return p, q, q_start
 
 
-def run_extend(p, q, q_start, max_new):
+def run_extend(p, q, q_start, max_new, workspace=None, stream=None):
     out = torch.full_like(q, float("nan"))
-    B.extend_attention(p, q, q_start, max_new, out)
+    B.extend_attention(p, q, q_start, max_new, out, stream, workspace)
     torch.cuda.synchronize()
     return out
+
+
+def extend_workspace(p, max_new):
+    """The workspace that problem p should bring, every byte part of a NaN."""
+    rc, n = B.rl_extend_attn_workspace_size(max_new, p.max_pages, p.batch, p.num_q_heads,
+                                            p.num_kv_heads)
+    assert rc == B.RL_DA_OK
+    return torch.full((n,), 0xff, dtype=torch.uint8, device=device())
 
 
 def oracle_extend(p, q, q_start, abs_values=False):
@@ -343,6 +351,38 @@ def test_extend_rows_do_not_depend_on_the_rest_of_the_batch(kv):
             at += n
 
 
+@pytest.mark.parametrize("divided", [False, True])
+@pytest.mark.parametrize("kv", ["bf16", "fp8_e4m3"])
+def test_extend_rows_do_not_depend_on_the_launch(kv, divided):
+    """Sequences long enough to be divided over their keys: the same bits alone
+    (8 work-groups), in a batch that fills the device (56 short neighbours, 488
+    work-groups of the undivided kernel), beside a neighbour of many new tokens
+    (a larger max_q_per_seq) and in a table of the context window's width, with
+    and without a workspace."""
+    new, prior = [7, 70, 1, 33, 100], [4200, 6200, 12300, 17000, 9000]
+    new += [1 + b % 5 for b in range(56)]
+    prior += [b % 16 for b in range(56)]
+    p, q, q_start = extend_problem(new, prior, seed=52, hq=32, hkv=8, kv=kv)
+    ws = extend_workspace(p, max(new)) if divided else None
+    full = run_extend(p, q, q_start, max(new), ws)
+    starts = q_start.cpu().numpy()
+    for rows, width in (([0], 0), ([1], 4096), ([2], 0), ([3], 0), ([4], 4096), ([3, 0, 2], 4096)):
+        idx = torch.as_tensor(rows, device=p.q.device)
+        table = torch.zeros((len(rows), max(width, p.max_pages)), dtype=torch.int32,
+                            device=device())
+        table[:, :p.max_pages] = p.block_table[idx]
+        sub = workloads.DecodeProblem(**{**p.__dict__, "batch": len(rows), "block_table": table,
+                                         "seq_lens": p.seq_lens[idx].contiguous()})
+        sub_new = [new[b] for b in rows]
+        sub_q = torch.cat([q[starts[b]:starts[b + 1]] for b in rows]).contiguous()
+        sub_start = torch.tensor(np.concatenate([[0], np.cumsum(sub_new)]), dtype=torch.int32,
+                                 device=device())
+        ws = extend_workspace(sub, max(sub_new)) if divided else None
+        got = run_extend(sub, sub_q, sub_start, max(sub_new), ws)
+        want = torch.cat([full[starts[b]:starts[b + 1]] for b in rows])
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)), (rows, width)
+
+
 # A sequence is divided over its keys from 4096 cached tokens on, if its new
 # tokens' rows (per kv head) number 512 at most; 2048 keys a split, 8 splits at most.
 SPLIT_CASES = [
@@ -364,7 +404,7 @@ def test_extend_divided_over_keys(case, kv, layout):
     print("case", case, kv, layout, flush=True)
     p, q, q_start = extend_problem(new, prior, seed=61 + case, hq=hq, hkv=hkv, kv=kv,
                                    layout=layout)
-    got = run_extend(p, q, q_start, max(new))
+    got = run_extend(p, q, q_start, max(new), extend_workspace(p, max(new)))
     check_extend(p, q, q_start, got, "divided %d %s" % (case, kv))
     dt = B.KV_DTYPES[kv]
 
@@ -383,11 +423,26 @@ def test_extend_divided_over_keys(case, kv, layout):
     small = call(B.rl_extend_attn_ws, workspace=ws, workspace_bytes=share)
     assert torch.equal(small.view(torch.int16), got.view(torch.int16))
     assert torch.all(ws[share:] == 0xff)
-    check_extend(p, q, q_start, call(B.rl_extend_attn), "undivided %d %s" % (case, kv))
-    b = 0
-    wide = torch.zeros((1, 4096), dtype=torch.int32, device=device())
-    wide[:, :p.max_pages] = p.block_table[b:b + 1]
-    sub = workloads.DecodeProblem(**{**p.__dict__, "batch": 1, "block_table": wide,
-                                     "seq_lens": p.seq_lens[b:b + 1].contiguous()})
-    alone = run_extend(sub, q[:new[b]].contiguous(), q_start[:2].contiguous(), new[b])
-    assert torch.equal(alone.view(torch.int16), got[:new[b]].view(torch.int16))
+    undivided = call(B.rl_extend_attn)
+    check_extend(p, q, q_start, undivided, "undivided %d %s" % (case, kv))
+    # the wrapper without a workspace, and on a stream that is not the current one
+    assert torch.equal(run_extend(p, q, q_start, max(new)).view(torch.int16),
+                       undivided.view(torch.int16))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    ws = extend_workspace(p, max(new))
+    torch.cuda.synchronize()
+    there = run_extend(p, q, q_start, max(new), ws, side)
+    assert torch.equal(there.view(torch.int16), got.view(torch.int16))
+    starts = q_start.cpu().numpy()
+    for b in range(len(new)):
+        if new[b] == 0:
+            continue
+        wide = torch.zeros((1, 4096), dtype=torch.int32, device=device())
+        wide[:, :p.max_pages] = p.block_table[b:b + 1]
+        sub = workloads.DecodeProblem(**{**p.__dict__, "batch": 1, "block_table": wide,
+                                         "seq_lens": p.seq_lens[b:b + 1].contiguous()})
+        alone = run_extend(sub, q[starts[b]:starts[b + 1]].contiguous(),
+                           q_start[b:b + 2] - q_start[b], new[b], extend_workspace(sub, new[b]))
+        assert torch.equal(alone.view(torch.int16),
+                           got[starts[b]:starts[b + 1]].view(torch.int16)), b

@@ -142,3 +142,44 @@ def test_extend_replays_equal_the_eager_launch(kv):
         torch.cuda.synchronize()
         assert same_bits(out, eager), "replay %d" % i
     del g
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("divided", [False, True])
+def test_extend_of_long_histories_replays_equal_the_eager_launch(kv, divided):
+    """Histories that a workspace divides over the keys (two launches, the split
+    kernel and its merge), captured with and without one on a stream that is
+    capturing: nothing is allocated in the call."""
+    new, prior = [5, 70, 33, 1], [300, 5000, 17, 12000]
+    lengths = [a + b for a, b in zip(new, prior)]
+    p = problem(32, 8, lengths, seed=330, kv=kv)
+    gen = torch.Generator().manual_seed(331)
+    q = torch.randn((sum(new), 32, 128), generator=gen).to(torch.bfloat16).to(device())
+    q_start = torch.tensor(np.concatenate([[0], np.cumsum(new)]), dtype=torch.int32,
+                           device=device())
+    rc, n = B.rl_extend_attn_workspace_size(max(new), p.max_pages, p.batch, 32, 8)
+    assert rc == B.RL_DA_OK and n > 0
+    ws = torch.full((n,), 0xff, dtype=torch.uint8, device=device()) if divided else None
+    eager = torch.full_like(q, float("nan"))
+    B.extend_attention(p, q, q_start, max(new), eager, None, ws)
+    torch.cuda.synchronize()
+    assert not torch.isnan(eager.float()).any()
+    out = torch.full_like(q, float("nan"))
+    held = []
+
+    def launch(s):
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        B.extend_attention(p, q, q_start, max(new), out, s, ws)
+        held.append(torch.cuda.memory_stats()["allocation.all.allocated"] - before)
+
+    g = capture(launch)
+    assert not any(held), held
+    for i in range(REPLAYS):
+        out.fill_(float("nan"))
+        if divided:
+            ws.fill_(0xff)
+        B.extend_attention(p, q, q_start, max(new), torch.empty_like(q), None, ws)
+        g.replay()
+        torch.cuda.synchronize()
+        assert same_bits(out, eager), "replay %d" % i
+    del g
