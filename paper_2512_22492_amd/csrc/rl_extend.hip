@@ -209,12 +209,22 @@ struct ExtendArgs {
     int32_t num_kv_heads;
     int32_t max_pages;
     int32_t num_tiles;          // ceil(max_q_per_seq / tile tokens)
-    int32_t split_slots;        // most splits of a sequence (SPLIT kernels)
-    int32_t split_tiles;        // tiles of a sequence that may be split
-    float* partials;            // [B][Hkv][split_tiles][split_slots] PartialTiles
     float scale_log2;           // |scale| * log2(e)
     uint32_t q_sign;            // 0x80008000 for a negative scale: Q enters negated
 };
+
+// What the SPLIT kernels take besides, behind the other arguments: in their midst
+// these fields took the undivided kernels a third scalar load before their
+// first stage, and 1.4% of their time (48 prompts of 100..2000 tokens, e4m3: 814.1
+// us, 825.8 with them).
+struct ExtendSplitArgs : ExtendArgs {
+    int32_t split_slots;        // most splits of a sequence
+    int32_t split_tiles;        // tiles of a sequence that may be split
+    float* partials;            // [B][Hkv][split_tiles][split_slots] PartialTiles
+};
+static_assert(sizeof(ExtendArgs) == 112, "what the undivided kernels take");
+template <bool SPLIT>
+using ExtendArgsOf = std::conditional_t<SPLIT, ExtendSplitArgs, ExtendArgs>;
 
 // Splits over the keys (SPLIT kernels, which have a workspace).  A tile walks its
 // keys one stage after another, about 1.4 us a stage when its CU holds no other,
@@ -231,7 +241,9 @@ struct ExtendArgs {
 // row and split, against 512 or 256 per key) stay below what its keys cost;
 // kSplitKeys keys a split, 32 stages against the 5-10 us of a unit's set-up and
 // ends.  A launch that fills the chip without them is better off with no
-// workspace (64 sequences of 32 new tokens after 4096: 207 us, 252 us cut).
+// workspace (64 sequences of 32 new tokens after 4096: 207 us, 252 us cut), and so
+// is one of short histories, whose grid is as wide as the table's splits: the
+// caller, who knows both, brings a workspace or none.
 constexpr int kSplitRows = 512;
 constexpr int kSplitKeys = 2048;
 constexpr int kMaxExtendSplits = 8;
@@ -255,7 +267,7 @@ struct PartialTile {
 // weight its values (l sums the unscaled probabilities), as in decode.
 template <int G, bool FP8, bool SPLIT>
 __global__ __launch_bounds__(kWave * kUnitWaves)
-__attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
+__attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgsOf<SPLIT> a)
 {
     static_assert(G >= 1 && G <= 16 && 16 % G == 0, "16-row blocks hold whole groups");
     constexpr int kTileTok = kTileRows / G;
@@ -278,7 +290,9 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
     // dealt first, so the shortest tiles fill the end of the launch.
     // A pair's later splits follow its tiles.
     const int T = a.num_tiles;
-    const int U = SPLIT ? T + (a.split_slots - 1) * a.split_tiles : T;  // units of a pair
+    int U = T;  // units of a pair
+    if constexpr (SPLIT)
+        U += (a.split_slots - 1) * a.split_tiles;
     const int g = blockIdx.x;
     const int main_units = (int)(gridDim.x / U / 8) * 8 * U;
     int bk, tile, split = 0;
@@ -289,9 +303,11 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
         bk = g / U;
         tile = T - 1 - g % U;
     }
-    if (SPLIT && tile < 0) {
-        split = 1 + (-1 - tile) / a.split_tiles;
-        tile = a.split_tiles - 1 - (-1 - tile) % a.split_tiles;
+    if constexpr (SPLIT) {
+        if (tile < 0) {
+            split = 1 + (-1 - tile) / a.split_tiles;
+            tile = a.split_tiles - 1 - (-1 - tile) % a.split_tiles;
+        }
     }
     // Pairs are taken longest sequence first, so that the longest tiles do
     // not start last and set the end of the launch.
@@ -846,27 +862,29 @@ __attribute__((amdgpu_waves_per_eu(2))) void extend_attn(ExtendArgs a)
     run(min(first_masked_stage, nstages), std::false_type{});
     run(nstages, std::true_type{});
 
-    if (SPLIT && nsplit > 1) {  // this split's rows, for merge_extend
-        PartialTile& part =
-            reinterpret_cast<PartialTile*>(a.partials)[(((int64_t)b * a.num_kv_heads + kvh) *
-                                                            a.split_tiles + tile) *
-                                                           a.split_slots + split];
+    if constexpr (SPLIT) {
+        if (nsplit > 1) {  // this split's rows, for merge_extend
+            PartialTile& part =
+                reinterpret_cast<PartialTile*>(a.partials)[(((int64_t)b * a.num_kv_heads + kvh) *
+                                                                a.split_tiles + tile) *
+                                                               a.split_slots + split];
 #pragma unroll
-        for (int rb = 0; rb < kRowBlocks; ++rb) {
-            const float l = FP8 ? sum_lanes_xor32(sum_lanes_xor16(lsum[rb])) : lacc[rb][0];
-            if (!row_real[rb])
-                continue;
-            const int r = wave * (kRowBlocks * 16) + rb * 16 + i16;
+            for (int rb = 0; rb < kRowBlocks; ++rb) {
+                const float l = FP8 ? sum_lanes_xor32(sum_lanes_xor16(lsum[rb])) : lacc[rb][0];
+                if (!row_real[rb])
+                    continue;
+                const int r = wave * (kRowBlocks * 16) + rb * 16 + i16;
 #pragma unroll
-            for (int db = 0; db < 8; ++db) {
-                const floatx4_t& v = o[rb][db];
-                *reinterpret_cast<float4*>(&part.acc[r][16 * db + 4 * g4]) =
-                    make_float4(v[0], v[1], v[2], v[3]);
+                for (int db = 0; db < 8; ++db) {
+                    const floatx4_t& v = o[rb][db];
+                    *reinterpret_cast<float4*>(&part.acc[r][16 * db + 4 * g4]) =
+                        make_float4(v[0], v[1], v[2], v[3]);
+                }
+                if (g4 == 0)
+                    part.ml[r] = make_float2(m_run[rb], l);
             }
-            if (g4 == 0)
-                part.ml[r] = make_float2(m_run[rb], l);
+            return;
         }
-        return;
     }
     // out[row] = O[row] / l[row]; lane holds row i16, dims 16db + 4g4 + jj.
 #pragma unroll
@@ -962,10 +980,8 @@ __global__ __launch_bounds__(kWave * kUnitWaves) void merge_extend(ExtendMergeAr
     }
 }
 
-typedef void (*ExtendKernel)(ExtendArgs);
-
 template <bool FP8, bool SPLIT>
-ExtendKernel extend_kernel(int G)
+auto extend_kernel(int G) -> void (*)(ExtendArgsOf<SPLIT>)
 {
     switch (G) {
     case 1: return extend_attn<1, FP8, SPLIT>;
@@ -1070,7 +1086,7 @@ rl_da_status rl_extend_attn_ws(const void* q, const int32_t* q_start, int32_t ma
     if (batch == 0 || max_q_per_seq == 0)
         return RL_DA_OK;
     const int tile_tok = kTileRows / G;
-    ExtendArgs ea;
+    ExtendSplitArgs ea;
     ea.q = (const uint16_t*)q;
     ea.q_start = q_start;
     ea.k_pool = (const uint8_t*)k_pool;
@@ -1114,14 +1130,18 @@ rl_da_status rl_extend_attn_ws(const void* q, const int32_t* q_start, int32_t ma
         seqs = (int32_t)grid_seqs;
     hipStream_t st = (hipStream_t)stream;
     const dim3 block(kWave * kUnitWaves);
-    const ExtendKernel k = split ? (fp8 ? extend_kernel<true, true>(G) : extend_kernel<false, true>(G))
-                                 : (fp8 ? extend_kernel<true, false>(G) : extend_kernel<false, false>(G));
     for (int32_t b0 = 0; b0 < batch; b0 += seqs) {
         const int32_t nb = batch - b0 < seqs ? batch - b0 : seqs;
         ea.q_start = q_start + b0;
         ea.seq_lens = seq_lens + b0;
         ea.block_table = block_table + (int64_t)b0 * max_pages;
-        hipLaunchKernelGGL(k, dim3((unsigned)(nb * num_kv_heads * units)), block, 0, st, ea);
+        const dim3 grid((unsigned)(nb * num_kv_heads * units));
+        if (split)
+            hipLaunchKernelGGL((fp8 ? extend_kernel<true, true>(G) : extend_kernel<false, true>(G)),
+                               grid, block, 0, st, ea);
+        else
+            hipLaunchKernelGGL((fp8 ? extend_kernel<true, false>(G) : extend_kernel<false, false>(G)),
+                               grid, block, 0, st, static_cast<const ExtendArgs&>(ea));
         if (hipGetLastError() != hipSuccess)
             return RL_DA_ERR_HIP;
         if (!split)
