@@ -1744,36 +1744,35 @@ int default_split_tokens(const rl_da_config* cfg, int64_t units_per_split)
     return st;
 }
 
-// Tokens of the shortest split that a handle with the default split size cuts a
-// sequence into (SplitRule), and whether sequences of up to one default split
-// stay whole.
+// Tokens of the shortest split that a handle cuts a sequence into, and whether
+// sequences of up to one default split stay whole.  With the default split size, on the
+// four-wavefront units and with a table of
+// 16 default splits and more, handles of up to 128 pairs of (sequence, kv head)
+// cut sequences by their length (SplitRule), over the partials that their rows
+// have anyway: even a full batch leaves CUs idle there, and a unit alone on its CU
+// draws 36 KB/us (2.1 MB in 58 us).  512 tokens a split: 64 x 1 pairs, lognormal around 4096, 73.5 -> 46.9
+// us; 16 x 8 pairs of 4096, 76 -> 57 us; four of those 16, 112 -> 17.5 us.  What it costs:
+// full batches of 9k..16k tokens each 5 to 10% (16 x 8 pairs of 9000: 106 -> 112 us;
+// caps of 8 and 12 splits and longer splits lost as much on ragged ones), and
+// short sequences in a table much wider than they are the merge launch that an
+// uncut table of one split does without (200 tokens in a table of 2048: 10.1 -> 13 us).
 //
-// A handle made for a long context has few long sequences in many of its
-// steps.  With 4096-token splits alone, three sequences of 8k..32k tokens x 8
-// heads are 120 units for 256 CUs, each a serial walk of about 110 us that
-// draws 26 KB/us, what one CU keeps in flight: 128.7 us a step, 78.7 us cut by
-// length (357 MB).  The line, from sweeps of the split size on one box:
-//   * up to 128 pairs of (sequence, kv head) even a full batch leaves CUs
-//     idle unless it is cut: 512 (64 x 1 pairs, lengths around 4096: 73.6 us at
-//     4096, 52.3 at 2048, 47.7 at 1024, 44.0 at 512, 44.9 at 256);
-//   * above that a full batch fills the chip and every cut costs it (64 x 8 pairs
-//     of 4096 tokens: 180.3 us whole, 184.1 at 2048, 196.3 at 512), so only
-//     sequences longer than one default split are cut, to 2048 at least;
-//   * and only where the table holds 16 default splits: in one made for its
-//     batch's longest sequence those above half its width take longer splits
-//     than the others and end the launch (128 x 4 pairs, lognormal to 32768
-//     in a table of 32768: 286 us whole, 311 us cut; 173 x 1 pairs of
-//     4k..22k tokens in a table of 22k: 227 us whole, 250 us cut).
+// Above that every unit's set-up and ends, about 4 us, and two units that share a
+// CU cost a batch that fills the chip uncut more than the cut gives it, and the
+// rule sees one length, never the batch: 2048-token splits of sequences above 4096
+// took 32 x 8 pairs of 6000 tokens from 131 to 154 us, 17 x 8 lognormal ones from 84 to
+// 110 us, 256 x 4 of 4k..12k (16 heads a group) from 399 to 437 us, and cutting only
+// those above 20480 tokens, into ten, 12 x 8 of 8k..32k from 162 to 182 us.  With 16
+// heads a group the same holds from 65 pairs on (32 x 4 of 9000: 112 -> 134 us).
 int min_split_tokens(const rl_da_config* cfg, int st, int max_splits, bool head_parallel,
                      bool* whole)
 {
-    *whole = true;
-    if (cfg->split_tokens != 0 || max_splits < 16 || head_parallel)
-        return st;
+    *whole = false;
     const int64_t pairs = (int64_t)cfg->max_batch * cfg->num_kv_heads;
-    *whole = pairs > 128;
-    const int fine = *whole ? 2048 : 512;
-    return fine < st ? fine : st;
+    const int64_t most_pairs = cfg->num_q_heads > 8 * cfg->num_kv_heads ? 64 : 128;
+    if (cfg->split_tokens != 0 || max_splits < 16 || head_parallel || pairs > most_pairs)
+        return st;
+    return st > 512 ? 512 : st;
 }
 
 // Token-major pools with at least two kv heads per work-group take the

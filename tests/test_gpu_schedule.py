@@ -152,10 +152,10 @@ def test_queue_is_reset_between_launches_of_any_shape():
 
 @pytest.mark.parametrize("kv,layout", [("bf16", "hnd"), ("fp8_e4m3", "nhd")])
 @pytest.mark.parametrize("max_batch,lengths", [
-    # 2 kv heads: 512-token splits from the shortest up (16 splits at most)
+    # 2 kv heads: splits of about 512 tokens (16 at most)
     (32, [0, 1, 511, 512, 513, 1025, 4095, 4096, 4097, 8191, 32768, 16, 0, 3000]),
-    # 2048-token splits, sequences of up to 4096 tokens whole
-    (200, [4096, 4097, 2049, 6145, 0, 20000, 32768, 7]),
+    # 400 pairs: not cut by length
+    (200, [4096, 4097, 2049, 6145, 0, 20000, 32768, 7, 20480, 20481]),
 ])
 def test_default_splits_follow_the_sequence_length(max_batch, lengths, kv, layout):
     """Handles with the default split size cut a sequence by its own length.
@@ -174,3 +174,14 @@ def test_default_splits_follow_the_sequence_length(max_batch, lengths, kv, layou
     print(check_close(bf16_to_f64(got), oracle_ref(p), "by length %d %s" % (max_batch, kv),
                       extra_abs=decode_extra(p, 0)))
     assert np.all(bf16_to_f64(got)[np.array(lengths) == 0] == 0)
+
+
+@pytest.mark.parametrize("hq,hkv,max_batch", [(8, 2, 65), (32, 2, 33), (4, 1, 300)])
+def test_handles_of_many_pairs_keep_whole_splits(hq, hkv, max_batch):
+    """Handles of more than 128 (sequence, kv head) pairs, 64 with 16 heads a group,
+    divide a sequence as an explicit 4096-token split does, bit for bit."""
+    p = problem(hq, hkv, [4097, 0, 30000, 6000, 20481, 12], seed=141 + hq, max_pages=2048)
+    with B.DecodeAttention(hq, hkv, max_batch, 4096) as attn, \
+            B.DecodeAttention(hq, hkv, max_batch, 4096, split_tokens=4096) as whole:
+        got, want = run_gpu(p, attn=attn), run_gpu(p, attn=whole)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
