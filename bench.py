@@ -168,7 +168,7 @@ def _pmc_means(path, counter):
 # Per measured operation: the kernel whose counters are summarised (name
 # prefix in the profiler's output) and the sources it is built from.
 OP_KERNELS = {
-    "attention": ("void (anonymous namespace)::split_", ("rl_common.h", "rl_decode.hip")),
+    "attention": ("void (anonymous namespace)::split_", ("rl_common.h", "rl_split_rule.h", "rl_decode.hip")),
     "pack": ("void (anonymous namespace)::copy_pieces<true>", ("rl_common.h", "rl_weight_sync.hip")),
 }
 

@@ -36,6 +36,7 @@
 #include <mutex>
 
 #include "rl_common.h"
+#include "rl_split_rule.h"
 
 using namespace rl_da;
 
@@ -66,27 +67,6 @@ enum Schedule : int32_t {
     kOnePerGroup = 0,   // grid = units: work-group g runs unit g (first splits first)
     kQueueInOrder = 1,  // persistent, units in sequence order (empty ones included)
     kQueuePlanned = 2,  // persistent, units longest first from the LDS plan
-};
-
-// How many pages each split of a sequence takes: `pages` for one that fills the
-// handle's table, and down to min_pages for a shorter one, so that it spreads
-// over the partials its rows have anyway (slots of them).  Sequences of up to
-// `whole` pages are not cut more finely than `pages`.  A function of the
-// sequence's own length and of the handle, never of the batch.
-struct SplitRule {
-    int32_t pages;      // the handle's split size
-    int32_t min_pages;  // == pages: every split takes that many
-    int32_t whole;      // 0 or pages
-    int32_t slots;      // splits of a sequence that fills the handle's table
-    __host__ __device__ bool by_length() const { return min_pages != pages; }
-    __host__ __device__ int pages_of(int npages) const
-    {
-        if (!by_length() || npages <= whole)
-            return pages;
-        const int even = (npages + slots - 1) / slots;
-        const int p = even > min_pages ? even : min_pages;
-        return p < pages ? p : pages;
-    }
 };
 
 struct SplitArgs {
@@ -1744,13 +1724,13 @@ int default_split_tokens(const rl_da_config* cfg, int64_t units_per_split)
     return st;
 }
 
-// Tokens of the shortest split that a handle cuts a sequence into, and whether
-// sequences of up to one default split stay whole.  With the default split size, on the
+// How a handle divides its sequences.  With the default split size, on the
 // four-wavefront units and with a table of
 // 16 default splits and more, handles of up to 128 pairs of (sequence, kv head)
 // cut sequences by their length (SplitRule), over the partials that their rows
 // have anyway: even a full batch leaves CUs idle there, and a unit alone on its CU
-// draws 36 KB/us (2.1 MB in 58 us).  512 tokens a split: 64 x 1 pairs, lognormal around 4096, 73.5 -> 46.9
+// draws 36 KB/us (2.1 MB in 58 us).  About 512 tokens a split, and no more splits
+// than give a full batch 2048 units: 64 x 1 pairs, lognormal around 4096, 73.5 -> 46.9
 // us; 16 x 8 pairs of 4096, 76 -> 57 us; four of those 16, 112 -> 17.5 us.  What it costs:
 // full batches of 9k..16k tokens each 5 to 10% (16 x 8 pairs of 9000: 106 -> 112 us;
 // caps of 8 and 12 splits and longer splits lost as much on ragged ones), and
@@ -1764,15 +1744,24 @@ int default_split_tokens(const rl_da_config* cfg, int64_t units_per_split)
 // 110 us, 256 x 4 of 4k..12k (16 heads a group) from 399 to 437 us, and cutting only
 // those above 20480 tokens, into ten, 12 x 8 of 8k..32k from 162 to 182 us.  With 16
 // heads a group the same holds from 65 pairs on (32 x 4 of 9000: 112 -> 134 us).
-int min_split_tokens(const rl_da_config* cfg, int st, int max_splits, bool head_parallel,
-                     bool* whole)
+SplitRule split_rule(const rl_da_config* cfg, int split_tokens, int max_splits, bool head_parallel)
 {
-    *whole = false;
+    SplitRule r;
+    r.pages = r.min_pages = split_tokens / kPageSize;
+    r.whole = 0;
+    r.most = max_splits;
     const int64_t pairs = (int64_t)cfg->max_batch * cfg->num_kv_heads;
-    const int64_t most_pairs = cfg->num_q_heads > 8 * cfg->num_kv_heads ? 64 : 128;
-    if (cfg->split_tokens != 0 || max_splits < 16 || head_parallel || pairs > most_pairs)
-        return st;
-    return st > 512 ? 512 : st;
+    const int64_t most_pairs =
+        cfg->num_q_heads > 8 * cfg->num_kv_heads ? 64 : 128;
+    if (cfg->split_tokens != 0 || head_parallel || max_splits < 16 || pairs > most_pairs ||
+        split_tokens < 1024)
+        return r;
+    r.min_pages = 512 / kPageSize;
+    r.whole = 3 * r.min_pages / 2 - 1;
+    const int64_t most = 2048 / pairs;
+    if (most < r.most)
+        r.most = (int)most;
+    return r;
 }
 
 // Token-major pools with at least two kv heads per work-group take the
@@ -1915,11 +1904,7 @@ rl_da_status init_handle(rl_decode_attn* h, const rl_da_config* cfg)
     h->use_mfma = (cfg->flags & RL_DA_SCORES_ON_VALU) == 0;
     h->head_parallel = uses_head_parallel(cfg);
     h->heads_per_unit = h->head_parallel ? heads_per_unit_for(cfg->num_kv_heads) : 1;
-    h->rule.pages = sp;
-    h->rule.slots = ms;
-    bool whole;
-    h->rule.min_pages = min_split_tokens(cfg, st, ms, h->head_parallel, &whole) / kPageSize;
-    h->rule.whole = whole ? sp : 0;
+    h->rule = split_rule(cfg, st, ms, h->head_parallel);
     for (int persistent = 0; persistent < 2; ++persistent)
         (persistent ? h->split_kernel_persistent : h->split_kernel) = select_split_kernel(
             G, (cfg->flags & RL_DA_CHECKED) != 0, cfg->kv_dtype == RL_DA_KV_FP8_E4M3, h->use_mfma,
@@ -2006,9 +1991,7 @@ rl_da_status enqueue_run(rl_decode_attn* h, const void* q, const void* k_pool,
     if (batch == 0)
         return RL_DA_OK;
 
-    const int shortest = max_pages <= h->rule.whole ? h->rule.pages : h->rule.min_pages;
-    const int most = (max_pages + shortest - 1) / shortest;
-    const int num_splits = most < h->max_splits ? most : h->max_splits;
+    const int num_splits = h->rule.splits_of(max_pages);
     const int64_t units = (int64_t)batch * (cfg.num_kv_heads / h->heads_per_unit) * num_splits;
     if (units + h->persistent_grid > INT32_MAX)
         return RL_DA_ERR_UNSUPPORTED;
