@@ -40,10 +40,10 @@
  * deterministic: no atomics take part in any reduction, a sequence's split size
  * is a function of the handle and of its own length and partial results merge
  * in a fixed order, so a sequence's output does not depend on the rest of the
- * batch or on where its
- * pages sit in the pool.  With several splits per sequence and more work
- * units than the device holds at once, the split kernel runs persistent
- * work-groups that take units, longest first, from a counter in the handle's
+ * batch or on where its pages sit in the pool.  With several splits per sequence
+ * and more work units than the device holds at once, the split kernel runs
+ * persistent work-groups that take units, longest first (by classes of an eighth
+ * of the split size), from a counter in the handle's
  * workspace (the last work-group of each launch resets it); which work-group
  * computes a unit never changes a result.
  *
@@ -156,9 +156,13 @@ typedef struct {
                                /* 4096, 2048, 1024, 512 that cuts max_batch   */
                                /* sequences of max_pages_per_seq pages into   */
                                /* >= 256 work-groups (a per-handle constant); */
-                               /* with 0 a sequence shorter than the table    */
-                               /* may be cut into shorter splits, as many at  */
-                               /* most as one that fills it                   */
+                               /* with 0, on a handle of up to 128 (sequence,  */
+                               /* kv head) pairs (64 if Hq / Hkv = 16) whose  */
+                               /* table takes 16 such splits and more, a      */
+                               /* sequence shorter than the table may be cut  */
+                               /* into shorter splits, as many at most as one */
+                               /* that fills it; not with RL_DA_PV_ON_VALU or */
+                               /* RL_DA_SCORES_ON_VALU                        */
     uint32_t flags;            /* RL_DA_CHECKED, RL_DA_SCORES_ON_VALU,        */
                                /* RL_DA_PER_HEAD_UNITS, RL_DA_PV_ON_VALU, 0   */
 } rl_da_config;
@@ -207,9 +211,9 @@ rl_da_status rl_decode_attn_workspace_size(const rl_da_config* cfg,
 rl_da_status rl_decode_attn_check_error(rl_decode_attn* h, int32_t* device_error);
 
 /* Split-K geometry of a handle: tokens per split and the number of splits a
- * block table of max_pages columns is divided into.  (With the default split
- * size, sequences shorter than the handle's table may take shorter splits, and
- * then more of them than this number.) */
+ * block table of max_pages columns is divided into.  (Handles that cut by
+ * length, see split_tokens: sequences shorter than the handle's table may take
+ * shorter splits, and then more of them than this number.) */
 rl_da_status rl_decode_attn_split_info(const rl_decode_attn* h, int32_t max_pages,
                                        int32_t* split_tokens, int32_t* num_splits);
 

@@ -14,7 +14,7 @@
 // sequence that fits one split is finished by one work-group; longer sequences
 // write one partial per split and a second kernel merges them.  How a
 // sequence's tokens are divided depends only on its own length and the
-// handle's split size, never on the rest of the batch.
+// handle (split_rule), never on the rest of the batch.
 //
 // Data movement is the whole cost: every K/V byte is read once from HBM.  A
 // (page, kv head) slab is 16 tokens x 128 dims x 2 bytes = 4 KiB, contiguous in
@@ -88,13 +88,14 @@ struct SplitArgs {
     int32_t num_q_heads;
     int32_t num_kv_heads;
     int32_t max_pages;
-    SplitRule rule;
-    int32_t num_splits;         // most splits of a sequence of max_pages pages
+    int32_t split_pages;
+    int32_t num_splits;         // ceil(max_pages / split_pages)
     int32_t heads_per_unit;     // kv heads per head-parallel work-group
     int32_t batch;
     int32_t schedule;           // several splits: a Schedule
     int32_t* queue;             // persistent launch: [0] next unit, [1] finished work-groups
     float scale_log2;           // scale * log2(e)
+    SplitRule rule;             // BY_LENGTH kernels (split_pages is then rule.pages)
 };
 
 // One wavefront's share of a work unit: pages p0 + wave + 4i, i < count.
@@ -103,7 +104,6 @@ struct WaveTask {
     int seq_len;   // clamped to max_pages * page_size
     int npages;    // pages holding the sequence
     int nsplit;    // splits of this sequence
-    int split_pages;  // pages of each but the last
     int p0;        // first page of the unit
     int count;     // pages of this wavefront (may be 0)
     bool owner;    // the one unit per (sequence, head) that writes an empty
@@ -116,9 +116,12 @@ struct WaveTask {
 // Entries past the sequence's end lie inside the table row and are loaded
 // but never used.  Returns false, for every wavefront of the unit alike, when
 // the unit holds no page of its sequence.
-template <bool CHECKED>
+// BY_LENGTH: a split's pages follow from the length; `pages` are what the plan
+// found, 0 without one, and only then do the entries of a split after the
+// first wait for the length.
+template <bool CHECKED, bool BY_LENGTH = false>
 __device__ __forceinline__ bool begin_unit(const SplitArgs& a, WaveTask& t, int32_t& my_page,
-                                           int b, int kvh, int s, bool owner)
+                                           int b, int kvh, int s, bool owner, int pages = 0)
 {
     t.lane = threadIdx.x % kWave;
     t.wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform: scalar
@@ -126,14 +129,14 @@ __device__ __forceinline__ bool begin_unit(const SplitArgs& a, WaveTask& t, int3
     t.kvh = kvh;
     t.owner = owner;
     t.s = max(s, 0);
-    t.split_pages = a.rule.pages;
-    t.p0 = t.s * t.split_pages;
+    int split_pages = BY_LENGTH && pages > 0 ? pages : a.split_pages;
+    t.p0 = t.s * split_pages;
     auto load_pages = [&] {
         const int col = t.p0 + t.wave + kUnitWaves * t.lane;
-        const bool in_split = col < t.p0 + t.split_pages && col < a.max_pages;
+        const bool in_split = col < t.p0 + split_pages && col < a.max_pages;
         my_page = in_split ? a.block_table[(int64_t)t.b * a.max_pages + col] : 0;
     };
-    const bool early = s >= 0 && !a.rule.by_length();
+    const bool early = BY_LENGTH ? s == 0 || pages > 0 : s >= 0;
     if (early)
         load_pages();  // issued together with the length load
     int L = a.seq_lens[t.b];
@@ -145,17 +148,22 @@ __device__ __forceinline__ bool begin_unit(const SplitArgs& a, WaveTask& t, int3
     }
     t.seq_len = L;
     t.npages = L > 0 ? (L + kPageSize - 1) / kPageSize : 0;
-    t.split_pages = a.rule.pages_of(t.npages);
-    t.nsplit = (t.npages + t.split_pages - 1) / t.split_pages;
-    if (s < 0)
+    if (BY_LENGTH && pages == 0)
+        split_pages = a.rule.pages_of(t.npages);
+    t.nsplit = (t.npages + split_pages - 1) / split_pages;
+    if (s < 0) {
+        if (t.nsplit == 0)
+            return false;
         t.s = t.nsplit - 1;
-    if (t.s < 0 || t.s >= t.nsplit)
+        t.p0 = t.s * split_pages;
+        load_pages();
+    } else if (t.s >= t.nsplit) {
         return false;
-    if (!early) {
-        t.p0 = t.s * t.split_pages;
+    } else if (!early) {
+        t.p0 = t.s * split_pages;
         load_pages();
     }
-    const int p1 = min(t.p0 + t.split_pages, t.npages);
+    const int p1 = min(t.p0 + split_pages, t.npages);
     t.count = max(0, (p1 - t.p0 - t.wave + kUnitWaves - 1) / kUnitWaves);
     if (CHECKED) {
         const bool bad = t.lane < t.count && (my_page < 0 || (int64_t)my_page >= a.num_pages);
@@ -191,6 +199,10 @@ __device__ __forceinline__ bool begin_unit(const SplitArgs& a, WaveTask& t, int3
 // sequence i/(U*num_splits) (kQueueInOrder) or, when every unit has a work-group of
 // its own (kOnePerGroup), split (i/U) / batch of sequence (i/U) % batch, empty ones
 // included.
+// Handles that split by length have full splits of many sizes: their plan lists
+// each sequence's full splits as one entry and its last split as another, all
+// entries by class (entry[e], and full[e] the units before it), and unit i is
+// found by binary search in full[].
 // Which work-group takes a unit never changes a result.
 
 // Exclusive prefix sum of data[0 .. n) in place by the work-group; returns
@@ -231,14 +243,15 @@ __device__ __forceinline__ int block_exclusive_scan(int* data, int n, int* tmp)
     return total;
 }
 
-constexpr int kLengthClasses = 8;
 constexpr int kMaxPlanWaves = kMaxHeadsPerUnit;  // wavefronts of the largest work-group
 
 // Ints of LDS the plan needs for `batch` sequences: full[], order[], one
-// byte per sequence for its length class, the scans' per-wavefront totals.
-__host__ __device__ constexpr int plan_ints(int batch)
+// byte per sequence for its length class, the scans' per-wavefront totals; by
+// length full[], entry[] and those totals.
+__host__ __device__ constexpr int plan_ints(int batch, bool by_length)
 {
-    return 2 * batch + 1 + (batch + 3) / 4 + kLengthClasses * kMaxPlanWaves;
+    return (by_length ? 4 * batch + 1 : 2 * batch + 1 + (batch + 3) / 4) +
+           kLengthClasses * kMaxPlanWaves;
 }
 
 // Full splits of sequence b and the length class of its last split (0 for
@@ -248,11 +261,10 @@ __device__ __forceinline__ void split_shape(const SplitArgs& a, int b, int& full
 {
     const int L = min(a.seq_lens[b], a.max_pages * kPageSize);
     const int np = L > 0 ? (L + kPageSize - 1) / kPageSize : 0;
-    const int sp = a.rule.pages_of(np);
-    const int ns = (np + sp - 1) / sp;
+    const int ns = (np + a.split_pages - 1) / a.split_pages;
     full = max(ns - 1, 0);
-    const int last = ns > 0 ? np - (ns - 1) * sp : 0;  // 0 .. sp <= rule.pages
-    cls = (a.rule.pages - last) * kLengthClasses / (a.rule.pages + 1);
+    const int last = ns > 0 ? np - (ns - 1) * a.split_pages : 0;  // 0 .. split_pages
+    cls = length_class(a.split_pages, last);
 }
 
 // Exclusive prefix over the work-group's threads of K counts per thread, in
@@ -348,13 +360,64 @@ __device__ __forceinline__ int build_plan(const SplitArgs& a, int* plan)
     return F;
 }
 
-// Runs unit(b, k, s, owner) -- k the unit's index within its (sequence,
-// split), s < 0 for a last split -- for every unit of the launch.  Work-group
+// The plan of a handle that splits by length (see above), a sequence a thread;
+// returns the number of its units per kv head.  One counting sort: a class's
+// counter holds its entries and, above kEntryBits, its units.  Ends with a barrier.
+__device__ __forceinline__ int build_plan_by_length(const SplitArgs& a, int* plan)
+{
+    constexpr int kEntryBits = 11;
+    static_assert(2 * kPlanBatchByLength < 1 << kEntryBits, "entries fit their bits");
+    static_assert(kPlanBatchByLength <= kWave * kUnitWaves, "a sequence a thread");
+    const int B = a.batch, b = threadIdx.x;
+    int* full = plan;
+    int* entry = plan + 2 * B + 1;
+    int* tmp = entry + 2 * B;
+    const int L = b < B ? min(a.seq_lens[b], a.max_pages * kPageSize) : 0;
+    const PlanShape shape(a.rule, L > 0 ? (L + kPageSize - 1) / kPageSize : 0);
+    const int full_count = b < B && shape.full > 0 ? shape.full << kEntryBits | 1 : 0;
+    const int last_count = b < B ? 1 << kEntryBits | 1 : 0;
+    int pos[kLengthClasses], total[kLengthClasses];
+#pragma unroll
+    for (int c = 0; c < kLengthClasses; ++c)
+        pos[c] = (shape.full_cls == c ? full_count : 0) + (shape.last_cls == c ? last_count : 0);
+    block_scan_counts(pos, total, tmp);
+    int start = 0;
+#pragma unroll
+    for (int c = 0; c < kLengthClasses; ++c) {
+        pos[c] += start;  // class c begins after every longer class
+        start += total[c];
+    }
+    auto place = [&](int cls, int count, int what) {
+        int at = 0;
+#pragma unroll
+        for (int c = 0; c < kLengthClasses; ++c) {
+            at = cls == c ? pos[c] : at;
+            pos[c] += cls == c ? count : 0;
+        }
+        const int e = at & ((1 << kEntryBits) - 1);
+        entry[e] = what;
+        full[e] = (int)((unsigned)at >> kEntryBits);
+    };
+    if (full_count > 0)
+        place(shape.full_cls, full_count, pack_entry(b, shape.pages, 0));
+    if (last_count > 0)
+        place(shape.last_cls, last_count, pack_entry(b, shape.pages, shape.full));
+    // past the last entry, so that a search may run over all 2 B
+    const int units = (int)((unsigned)start >> kEntryBits);
+    for (int e = (start & ((1 << kEntryBits) - 1)) + threadIdx.x; e < 2 * B + 1; e += blockDim.x)
+        full[e] = units;
+    __syncthreads();
+    return units;
+}
+
+// Runs unit(b, k, s, owner, pages) -- k the unit's index within its (sequence,
+// split), s < 0 for a last split, pages those of its splits if a plan by length
+// found them (else 0) -- for every unit of the launch.  Work-group
 // g starts with unit g; later units come from a.queue (gridDim.x + the
 // count of earlier requests), requested when the current unit starts and
 // needed only when it ends.  The last work-group to finish resets the queue
 // for the next launch.  plan: the dynamic LDS (unused without a plan).
-template <typename Unit>
+template <bool BY_LENGTH = false, typename Unit>
 __device__ __forceinline__ void run_persistent(const SplitArgs& a, int U, int* plan, Unit unit)
 {
     if (a.schedule == kOnePerGroup) {
@@ -371,7 +434,10 @@ __device__ __forceinline__ void run_persistent(const SplitArgs& a, int U, int* p
     unsigned* const counter = reinterpret_cast<unsigned*>(&a.queue[0]);
     const bool planned = a.schedule == kQueuePlanned;
     int F = 0, total;
-    if (planned) {
+    if (planned && BY_LENGTH) {
+        F = build_plan_by_length(a, plan);
+        total = F * U;
+    } else if (planned) {
         F = build_plan(a, plan);
         total = (F + a.batch) * U;
     } else {
@@ -389,13 +455,14 @@ __device__ __forceinline__ void run_persistent(const SplitArgs& a, int U, int* p
             next = atomicInc(counter, 0xffffffffu);
         const int k = item % U, j = item / U;
         int b, s;
+        [[maybe_unused]] int pages = 0;  // of the sequence's splits, if the plan knows
         bool owner;
         if (!planned) {
             s = j % a.num_splits;
             b = j / a.num_splits;
             owner = s == 0;
-        } else if (j < F) {
-            int lo = 0, hi = a.batch;  // full[lo] <= j < full[hi]
+        } else if (BY_LENGTH || j < F) {
+            int lo = 0, hi = BY_LENGTH ? 2 * a.batch : a.batch;  // full[lo] <= j < full[hi]
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
                 if (full[mid] <= j)
@@ -406,6 +473,13 @@ __device__ __forceinline__ void run_persistent(const SplitArgs& a, int U, int* p
             b = lo;
             s = j - full[lo];
             owner = false;
+            if (BY_LENGTH) {
+                int first;
+                unpack_entry(plan[2 * a.batch + 1 + lo], b, pages, first);
+                pages = __builtin_amdgcn_readfirstlane(pages);
+                s += first;
+                owner = s == 0;
+            }
         } else {
             b = order[j - F];
             s = -1;
@@ -413,8 +487,12 @@ __device__ __forceinline__ void run_persistent(const SplitArgs& a, int U, int* p
         }
         b = __builtin_amdgcn_readfirstlane(b);
         s = __builtin_amdgcn_readfirstlane(s);
-        if (b >= 0 && b < a.batch && s < a.num_splits)  // holds by construction
-            unit(a, b, k, s, owner);
+        if (b >= 0 && b < a.batch && s < a.num_splits) {  // holds by construction
+            if constexpr (BY_LENGTH)
+                unit(a, b, k, s, owner, pages);
+            else
+                unit(a, b, k, s, owner);
+        }
         if (threadIdx.x == 0)
             s_item[cur] = (int)gridDim.x + (int)next;
         __syncthreads();
@@ -971,12 +1049,12 @@ __device__ __forceinline__ bool begin_unit_hp(const SplitArgs& a, WaveTask& t, i
     t.b = b;
     t.owner = owner;
     t.s = max(s, 0);
-    t.p0 = t.s * a.rule.pages;
+    t.p0 = t.s * a.split_pages;
     // the first kWave pages' block-table entries (later ones are loaded as
     // the wavefront reaches them)
     auto load_pages = [&] {
         const int col = t.p0 + t.lane;
-        const bool in_split = t.lane < a.rule.pages && col < a.max_pages;
+        const bool in_split = t.lane < a.split_pages && col < a.max_pages;
         my_page = in_split ? a.block_table[(int64_t)t.b * a.max_pages + col] : 0;
     };
     if (s >= 0)
@@ -990,15 +1068,15 @@ __device__ __forceinline__ bool begin_unit_hp(const SplitArgs& a, WaveTask& t, i
     }
     t.seq_len = L;
     t.npages = L > 0 ? (L + kPageSize - 1) / kPageSize : 0;
-    t.nsplit = (t.npages + a.rule.pages - 1) / a.rule.pages;
+    t.nsplit = (t.npages + a.split_pages - 1) / a.split_pages;
     if (s < 0) {
         if (t.nsplit == 0)
             return false;
         t.s = t.nsplit - 1;
-        t.p0 = t.s * a.rule.pages;
+        t.p0 = t.s * a.split_pages;
         load_pages();
     }
-    const int p1 = min(t.p0 + a.rule.pages, t.npages);
+    const int p1 = min(t.p0 + a.split_pages, t.npages);
     if (t.p0 >= p1)
         return false;
     t.count = p1 - t.p0;
@@ -1473,7 +1551,11 @@ __device__ __forceinline__ void attend_pages_pv(const SplitArgs& a, const WaveTa
         l_row[e] = row16_sum(lsum[e]);
 }
 
-template <int G, bool CHECKED, typename KV, bool PERSISTENT>
+// BY_LENGTH: the handles whose splits follow the sequence's length.  A kernel of
+// its own, since the rule costs scalar registers: kernels that carry it for
+// handles that never use it spill more of them (G = 16 e4m3: 10 -> 16; 16 x 4 pairs of
+// 4500 tokens 69 -> 72 us).
+template <int G, bool CHECKED, typename KV, bool PERSISTENT, bool BY_LENGTH = false>
 __global__ __launch_bounds__(kWave * kUnitWaves)
 __attribute__((amdgpu_waves_per_eu(G > 4 || PERSISTENT ? 2 : 3))) void split_pv(SplitArgs a)
 {
@@ -1483,10 +1565,10 @@ __attribute__((amdgpu_waves_per_eu(G > 4 || PERSISTENT ? 2 : 3))) void split_pv(
     __shared__ __attribute__((aligned(16))) PvShared<G> sh;
     extern __shared__ int plan[];
 
-    auto unit = [&](const SplitArgs& a, int b, int kvh, int s, bool owner) {
+    auto unit = [&](const SplitArgs& a, int b, int kvh, int s, bool owner, int pages = 0) {
         WaveTask t;
         int32_t my_page;
-        if (!begin_unit<CHECKED>(a, t, my_page, b, kvh, s, owner)) {
+        if (!begin_unit<CHECKED, BY_LENGTH>(a, t, my_page, b, kvh, s, owner, pages)) {
             write_zero_rows<G>(a, t);
             return;
         }
@@ -1517,7 +1599,7 @@ __attribute__((amdgpu_waves_per_eu(G > 4 || PERSISTENT ? 2 : 3))) void split_pv(
         merge_unit<G>(a, t, sh.unit);
     };
     if (PERSISTENT)
-        run_persistent(a, a.num_kv_heads, plan, unit);
+        run_persistent<BY_LENGTH>(a, a.num_kv_heads, plan, unit);
     else  // one split per sequence: unit (b, kv head) = blockIdx.x
         unit(a, blockIdx.x / a.num_kv_heads, blockIdx.x % a.num_kv_heads, 0, true);
 }
@@ -1646,13 +1728,13 @@ typedef void (*SplitKernel)(SplitArgs);
 
 // PERSISTENT: the kernel for runs with more than one split (persistent
 // work-groups taking units from the queue).  pv: the P.V product on the
-// matrix cores.
-template <int G, bool CHECKED, bool PERSISTENT>
+// matrix cores.  BY_LENGTH: splits that follow the length (pv only).
+template <int G, bool CHECKED, bool PERSISTENT, bool BY_LENGTH>
 SplitKernel pick(bool fp8, bool mfma, bool hp, bool pv)
 {
-    if (pv)
-        return fp8 ? split_pv<G, CHECKED, KvFp8Rows, PERSISTENT>
-                   : split_pv<G, CHECKED, KvBf16, PERSISTENT>;
+    if (BY_LENGTH || pv)
+        return fp8 ? split_pv<G, CHECKED, KvFp8Rows, PERSISTENT, BY_LENGTH>
+                   : split_pv<G, CHECKED, KvBf16, PERSISTENT, BY_LENGTH>;
     if (hp)
         return fp8 ? split_mfma_hp<G, CHECKED, KvFp8, PERSISTENT>
                    : split_mfma_hp<G, CHECKED, KvBf16, PERSISTENT>;
@@ -1663,24 +1745,27 @@ SplitKernel pick(bool fp8, bool mfma, bool hp, bool pv)
     return split_valu_bf16<G, CHECKED, PERSISTENT>;
 }
 
-template <bool CHECKED, bool PERSISTENT>
+template <bool CHECKED, bool PERSISTENT, bool BY_LENGTH = false>
 SplitKernel select_for_group(int G, bool fp8, bool mfma, bool hp, bool pv)
 {
     switch (G) {
-    case 1: return pick<1, CHECKED, PERSISTENT>(fp8, mfma, hp, pv);
-    case 2: return pick<2, CHECKED, PERSISTENT>(fp8, mfma, hp, pv);
-    case 4: return pick<4, CHECKED, PERSISTENT>(fp8, mfma, hp, pv);
-    case 8: return pick<8, CHECKED, PERSISTENT>(fp8, mfma, hp, pv);
+    case 1: return pick<1, CHECKED, PERSISTENT, BY_LENGTH>(fp8, mfma, hp, pv);
+    case 2: return pick<2, CHECKED, PERSISTENT, BY_LENGTH>(fp8, mfma, hp, pv);
+    case 4: return pick<4, CHECKED, PERSISTENT, BY_LENGTH>(fp8, mfma, hp, pv);
+    case 8: return pick<8, CHECKED, PERSISTENT, BY_LENGTH>(fp8, mfma, hp, pv);
     case 16:  // only the matrix-core value pass holds 16 heads' accumulators
-        return fp8 ? split_pv<16, CHECKED, KvFp8Rows, PERSISTENT>
-                   : split_pv<16, CHECKED, KvBf16, PERSISTENT>;
+        return fp8 ? split_pv<16, CHECKED, KvFp8Rows, PERSISTENT, BY_LENGTH>
+                   : split_pv<16, CHECKED, KvBf16, PERSISTENT, BY_LENGTH>;
     default: return nullptr;
     }
 }
 
 SplitKernel select_split_kernel(int G, bool checked, bool fp8, bool mfma, bool hp, bool pv,
-                               bool persistent)
+                               bool persistent, bool by_length)
 {
+    if (persistent && by_length)
+        return checked ? select_for_group<true, true, true>(G, fp8, mfma, hp, pv)
+                       : select_for_group<false, true, true>(G, fp8, mfma, hp, pv);
     if (checked)
         return persistent ? select_for_group<true, true>(G, fp8, mfma, hp, pv)
                           : select_for_group<true, false>(G, fp8, mfma, hp, pv);
@@ -1725,7 +1810,7 @@ int default_split_tokens(const rl_da_config* cfg, int64_t units_per_split)
 }
 
 // How a handle divides its sequences.  With the default split size, on the
-// four-wavefront units and with a table of
+// default path (four-wavefront units, P.V on the matrix cores) and with a table of
 // 16 default splits and more, handles of up to 128 pairs of (sequence, kv head)
 // cut sequences by their length (SplitRule), over the partials that their rows
 // have anyway: even a full batch leaves CUs idle there, and a unit alone on its CU
@@ -1744,7 +1829,7 @@ int default_split_tokens(const rl_da_config* cfg, int64_t units_per_split)
 // 110 us, 256 x 4 of 4k..12k (16 heads a group) from 399 to 437 us, and cutting only
 // those above 20480 tokens, into ten, 12 x 8 of 8k..32k from 162 to 182 us.  With 16
 // heads a group the same holds from 65 pairs on (32 x 4 of 9000: 112 -> 134 us).
-SplitRule split_rule(const rl_da_config* cfg, int split_tokens, int max_splits, bool head_parallel)
+SplitRule split_rule(const rl_da_config* cfg, int split_tokens, int max_splits, bool pv)
 {
     SplitRule r;
     r.pages = r.min_pages = split_tokens / kPageSize;
@@ -1752,9 +1837,9 @@ SplitRule split_rule(const rl_da_config* cfg, int split_tokens, int max_splits, 
     r.most = max_splits;
     const int64_t pairs = (int64_t)cfg->max_batch * cfg->num_kv_heads;
     const int64_t most_pairs =
-        cfg->num_q_heads > 8 * cfg->num_kv_heads ? 64 : 128;
-    if (cfg->split_tokens != 0 || head_parallel || max_splits < 16 || pairs > most_pairs ||
-        split_tokens < 1024)
+        cfg->num_q_heads > 8 * cfg->num_kv_heads ? kPlanBatchByLength / 2 : kPlanBatchByLength;
+    if (cfg->split_tokens != 0 || !pv || max_splits < 16 || max_splits > kPlanSplitsByLength ||
+        pairs > most_pairs || split_tokens < 1024)
         return r;
     r.min_pages = 512 / kPageSize;
     r.whole = 3 * r.min_pages / 2 - 1;
@@ -1904,11 +1989,12 @@ rl_da_status init_handle(rl_decode_attn* h, const rl_da_config* cfg)
     h->use_mfma = (cfg->flags & RL_DA_SCORES_ON_VALU) == 0;
     h->head_parallel = uses_head_parallel(cfg);
     h->heads_per_unit = h->head_parallel ? heads_per_unit_for(cfg->num_kv_heads) : 1;
-    h->rule = split_rule(cfg, st, ms, h->head_parallel);
+    const bool pv = !h->head_parallel && uses_pv_mfma(cfg);
+    h->rule = split_rule(cfg, st, ms, pv);
     for (int persistent = 0; persistent < 2; ++persistent)
         (persistent ? h->split_kernel_persistent : h->split_kernel) = select_split_kernel(
             G, (cfg->flags & RL_DA_CHECKED) != 0, cfg->kv_dtype == RL_DA_KV_FP8_E4M3, h->use_mfma,
-            h->head_parallel, !h->head_parallel && uses_pv_mfma(cfg), persistent != 0);
+            h->head_parallel, pv, persistent != 0, h->rule.by_length());
     if (hipGetDevice(&h->device) != hipSuccess)
         return RL_DA_ERR_HIP;
     // One persistent work-group per slot that can be resident with the
@@ -1916,7 +2002,7 @@ rl_da_status init_handle(rl_decode_attn* h, const rl_da_config* cfg)
     // the static grid keeps resident.
     const int threads = h->head_parallel ? kWave * h->heads_per_unit : kWave * kUnitWaves;
     const int plan_batch = cfg->max_batch < kMaxPlanBatch ? cfg->max_batch : kMaxPlanBatch;
-    const size_t lds = (size_t)plan_ints(plan_batch) * sizeof(int);
+    const size_t lds = (size_t)plan_ints(plan_batch, h->rule.by_length()) * sizeof(int);
     int per_cu = 0, static_per_cu = 0, cus = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
             &per_cu, reinterpret_cast<const void*>(h->split_kernel_persistent), threads, lds) !=
@@ -2035,13 +2121,14 @@ rl_da_status enqueue_run(rl_decode_attn* h, const void* q, const void* k_pool,
     sa.num_q_heads = cfg.num_q_heads;
     sa.num_kv_heads = cfg.num_kv_heads;
     sa.max_pages = max_pages;
-    sa.rule = h->rule;
+    sa.split_pages = h->split_pages;
     sa.num_splits = num_splits;
     sa.heads_per_unit = h->heads_per_unit;
     sa.batch = batch;
     sa.schedule = schedule;
     sa.queue = h->queue;
     sa.scale_log2 = scale * kLog2e;
+    sa.rule = h->rule;
 
     h->last_stream = st;
     const int threads = h->head_parallel ? kWave * h->heads_per_unit : kWave * kUnitWaves;
@@ -2055,7 +2142,9 @@ rl_da_status enqueue_run(rl_decode_attn* h, const void* q, const void* k_pool,
                                  ? units
                                  : h->persistent_grid;
         const size_t lds =
-            schedule == kQueuePlanned ? (size_t)plan_ints(batch) * sizeof(int) : 0;
+            schedule == kQueuePlanned
+                ? (size_t)plan_ints(batch, h->rule.by_length()) * sizeof(int)
+                : 0;
         if (launch_split(h, h->split_kernel_persistent, grid, threads, lds, st, sa) !=
             hipSuccess)
             return RL_DA_ERR_HIP;

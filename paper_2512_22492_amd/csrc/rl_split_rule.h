@@ -1,6 +1,6 @@
-// rl_split_rule.h -- how a decode handle divides a sequence into splits.  Plain
-// integer functions of the handle and of a sequence's length, for the host and
-// the device.
+// rl_split_rule.h -- how a decode handle divides a sequence into splits, and in
+// which order a launch takes them.  Plain integer functions of the handle and
+// of a sequence's length, for the host and the device.
 
 #pragma once
 
@@ -13,6 +13,9 @@
 #endif
 
 namespace rl_da {
+
+// Classes of split sizes, longest first; a launch takes its units by class.
+constexpr int kLengthClasses = 8;
 
 // How a sequence's pages are divided.  Every split takes `pages` and the last one
 // what is left; of a handle that splits by length, sequences of more than
@@ -44,5 +47,45 @@ struct SplitRule {
         return (npages + n - 1) / n;
     }
 };
+
+// Class of a split of `n` pages: 0 for one of the handle's split size, rising as
+// it gets shorter; an empty sequence's is the last.
+RL_HD inline int length_class(int pages, int n)
+{
+    return (pages - n) * kLengthClasses / (pages + 1);
+}
+
+// What the plan of a launch holds of a sequence of npages pages, on a handle that
+// splits by length: its full splits (none of a sequence of one split) and its
+// last one, each with the class it is taken in.  An empty sequence counts one
+// split, whose unit writes its zeros.
+struct PlanShape {
+    int pages;     // of each split but the last
+    int full;      // splits before the last one
+    int full_cls;
+    int last_cls;
+    RL_HD PlanShape(const SplitRule& r, int npages) : pages(r.pages_of(npages))
+    {
+        const int n = (npages + pages - 1) / pages;
+        full = n > 1 ? n - 1 : 0;
+        full_cls = length_class(r.pages, pages);
+        last_cls = length_class(r.pages, npages - full * pages);
+    }
+};
+
+// An entry of that plan in 32 bits: the sequence, the pages of its splits and the
+// number of the entry's first split.
+constexpr int kPlanBatchByLength = 128;  // sequences a plan by length can hold
+constexpr int kPlanSplitsByLength = 1 << 11;  // splits of a sequence
+RL_HD inline int pack_entry(int b, int pages, int split)
+{
+    return (int)((uint32_t)split << 19 | (uint32_t)pages << 10 | (uint32_t)b);
+}
+RL_HD inline void unpack_entry(int entry, int& b, int& pages, int& split)
+{
+    b = entry & 1023;
+    pages = entry >> 10 & 511;
+    split = (int)((uint32_t)entry >> 19);
+}
 
 }  // namespace rl_da

@@ -185,3 +185,51 @@ def test_handles_of_many_pairs_keep_whole_splits(hq, hkv, max_batch):
             B.DecodeAttention(hq, hkv, max_batch, 4096, split_tokens=4096) as whole:
         got, want = run_gpu(p, attn=attn), run_gpu(p, attn=whole)
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+def ragged(n, top, seed):
+    rng = np.random.default_rng(seed)
+    L = np.exp(rng.uniform(0, np.log(top), n)).astype(int)
+    L[::9] = 0
+    return [int(x) for x in L]
+
+
+@pytest.mark.parametrize("flags", [0, B.RL_DA_CHECKED])
+@pytest.mark.parametrize("hq,hkv,kv,layout", [(8, 2, "bf16", "hnd"), (32, 2, "fp8_e4m3", "hnd"),
+                                              (2, 2, "fp8_e4m3", "nhd")])
+@pytest.mark.parametrize("max_batch,top,seen", [
+    # 64 pairs: up to 32 splits
+    (32, 40000, 2500),
+    # 128 pairs: more units than the chip holds, splits of 512 to 4096 tokens
+    (64, 40000, 2500),
+    # 512 pairs: not cut by length
+    (256, 24000, 1500),
+    # 128 pairs in a table of one default split: a work-group per unit
+    (64, 4096, 256),
+])
+def test_splits_by_length_of_many_sequences(max_batch, top, seen, hq, hkv, kv, layout, flags):
+    """Launches that the queue plans, by length (entries of full and last splits by
+    class; up to 64 pairs with 16 heads a group) and not, and the static grid of
+    a table of one default split, against the oracle; sequences alone, in a
+    table as wide as the handle's, give the same bits."""
+    lengths = ragged(max_batch, min(top, 4096), seed=max_batch + top)
+    lengths[3], lengths[5], lengths[-1] = top, top - 17, min(4097, top)
+    lengths[6], lengths[7], lengths[8] = top // 2, top - 3000, top // 3
+    print("case", max_batch, top, hq, kv, layout, flags, flush=True)
+    p = problem(hq, hkv, lengths, seed=111 + top, kv=kv, layout=layout, max_pages=seen)
+    with B.DecodeAttention(hq, hkv, max_batch, 4096, kv_dtype=kv, layout=layout,
+                           flags=flags | B.RL_DA_PER_HEAD_UNITS) as attn:
+        assert attn.unit_heads() == 1 and attn.split_info(4096) == (4096, 16)
+        got = run_gpu(p, attn=attn)
+        for rows in ([3], [5, 1], list(range(0, max_batch, 7))):
+            sub = sub_problem(p, rows)
+            wide = torch.zeros((len(rows), 4096), dtype=torch.int32, device=device())
+            wide[:, :seen] = sub.block_table
+            sub.block_table = wide
+            assert torch.equal(run_gpu(sub, attn=attn).view(torch.int16),
+                               got[rows].view(torch.int16)), rows
+        if flags & B.RL_DA_CHECKED:
+            assert attn.check_error() == 0
+    print(check_close(bf16_to_f64(got), oracle_ref(p), "by length, many",
+                      extra_abs=decode_extra(p, flags)))
+    assert np.all(bf16_to_f64(got)[np.array(lengths) == 0] == 0)
