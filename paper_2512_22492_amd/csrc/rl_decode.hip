@@ -1614,13 +1614,16 @@ __attribute__((amdgpu_waves_per_eu(G > 4 || PERSISTENT ? 2 : 3))) void split_pv(
 //
 // A launch whose handle allows several splits may hold only sequences of one:
 // its work-groups find that from the length alone and leave, so what such a
-// launch costs is its number of work-groups (200 sequences x 64 heads, all of
-// one split: 7.8 us with a
-// work-group a row; the step 58.4 -> 54.2 us).  Hence several rows of a sequence per work-group once
-// there are more rows than keep the chip busy (kMergeGroups).
+// launch costs is its number of work-groups.  Hence several rows of a sequence per
+// work-group once there are more rows than keep the chip busy (kMergeGroups), but
+// kMergeRows at most, since a row's loads wait for the row before it: 1024
+// sequences x 64 heads, e4m3, of one split each (a step of 192 us with a
+// work-group a row) 170.8 / 174.1 / 178.5 us with up to 64 / 8 / 4 rows; of 4k..12k
+// tokens, two or three splits each, 1648 / 1616 / 1617 us.
 
 constexpr int kMergeWaves = 4;
 constexpr int64_t kMergeGroups = 1024;
+constexpr int kMergeRows = 8;
 
 struct MergeArgs {
     const int32_t* seq_lens;
@@ -1635,11 +1638,12 @@ struct MergeArgs {
 };
 
 // Rows per work-group: doubled while they divide the heads and leave at least
-// kMergeGroups work-groups.
+// kMergeGroups work-groups; kMergeRows at most.
 int merge_rows(int64_t batch, int num_q_heads)
 {
     int rows = 1;
-    while (num_q_heads % (2 * rows) == 0 && batch * num_q_heads / (2 * rows) >= kMergeGroups)
+    while (2 * rows <= kMergeRows && num_q_heads % (2 * rows) == 0 &&
+           batch * num_q_heads / (2 * rows) >= kMergeGroups)
         rows *= 2;
     return rows;
 }

@@ -233,3 +233,19 @@ def test_splits_by_length_of_many_sequences(max_batch, top, seen, hq, hkv, kv, l
     print(check_close(bf16_to_f64(got), oracle_ref(p), "by length, many",
                       extra_abs=decode_extra(p, flags)))
     assert np.all(bf16_to_f64(got)[np.array(lengths) == 0] == 0)
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+def test_merge_of_many_rows(splits):
+    """Batches whose merge takes up to eight heads of a sequence a work-group, of
+    one split each and of two or three, among them empty sequences."""
+    rng = np.random.default_rng(splits)
+    lengths = [int(x) for x in rng.integers(0, 100 if splits == 1 else 190, 513)]
+    lengths[0], lengths[-1] = 0, 129
+    p = problem(32, 2, lengths, seed=121 + splits, max_pages=12)
+    got = run_gpu(p, split_tokens=64 if splits == 2 else 128)
+    print(check_close(bf16_to_f64(got), oracle_ref(p), "merge rows", extra_abs=decode_extra(p, 0)))
+    assert np.all(bf16_to_f64(got)[np.array(lengths) == 0] == 0)
+    rows = [1, 300, 512]
+    part = run_gpu(sub_problem(p, rows), split_tokens=64 if splits == 2 else 128)
+    assert torch.equal(part.view(torch.int16), got[rows].view(torch.int16))
